@@ -19,7 +19,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libddi.so")
-SOURCES = ["plan.cpp", "fft.hip", "nufft.hip", "gpe.hip", "capi.cpp"]
+SOURCES = ["plan.cpp", "rings.cpp", "fft.hip", "nufft.hip", "rings.hip", "gpe.hip", "capi.cpp"]
 
 
 def hipcc():
@@ -41,7 +41,7 @@ def build(verbose: bool = False) -> str:
     cc = hipcc()
 
     def one(src):
-        obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
+        obj = os.path.join(OBJ, src + ".o")
         cmd = [cc, "-x", "hip", *common_flags(), "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)

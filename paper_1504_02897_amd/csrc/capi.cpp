@@ -53,10 +53,15 @@ void free_plan(ddi::DevicePlan& P) {
   if (P.aux) (void)hipStreamDestroy(P.aux);
   void* ptrs[] = {P.nodes, P.c_scaled, P.c_half, P.ones, P.fine_short, P.kq, P.base_scaled, P.base_half,
                   P.deconv[0], P.deconv[1], P.deconv[2],
-                  P.fine, P.gnodes, P.partial, P.ipartial, P.pads, P.gpe.rho, P.gpe.phi, P.gpe.phit, P.gpe.c1, P.gpe.c2, P.gpe.red};
+                  P.fine, P.gnodes, P.partial, P.ipartial, P.pads, P.xyw, P.ring_wz, P.gpe.rho, P.gpe.phi, P.gpe.phit, P.gpe.c1, P.gpe.c2, P.gpe.red};
   for (auto& d : P.dsched) {
-    void* sp[] = {d.list, d.items, d.reduces, d.interp_items, d.interp_direct, d.gptr, d.gpos, d.ent};
+    void* sp[] = {d.list, d.items, d.reduces, d.interp_items, d.interp_direct, d.ent};
     for (void* p : sp)
+      if (p) (void)hipFree(p);
+  }
+  for (auto& d : P.drings) {
+    void* rp[] = {d.refs, d.ent, d.interp, d.interp_cut, d.gptr, d.gpos};
+    for (void* p : rp)
       if (p) (void)hipFree(p);
   }
   for (void* p : ptrs)
@@ -66,22 +71,11 @@ void free_plan(ddi::DevicePlan& P) {
 }
 
 template <typename T>
-ddi_status build_device(ddi::DevicePlan& P, hipStream_t s, std::vector<ddi::NodeRec<T>>& recs,
-                        std::vector<std::vector<ddi::Complex<T>>>& tws, std::vector<T>& padrows) {
+ddi_status build_device(ddi::DevicePlan& P, hipStream_t s, const ddi::RingTables& rings,
+                        std::vector<ddi::NodeRec<T>>& recs, std::vector<std::vector<ddi::Complex<T>>>& tws,
+                        std::vector<T>& rows, std::vector<double>& xyw) {
   const ddi::HostTables& H = P.H;
   int64_t& bytes = P.workspace_bytes;
-  recs.resize(H.M);
-  for (int64_t q = 0; q < H.M; ++q) {
-    ddi::NodeRec<T>& r = recs[q];
-    std::memset(&r, 0, sizeof(r));
-    for (int a = 0; a < 3; ++a) {
-      r.l0[a] = H.l0[3 * q + a];
-      for (int i = 0; i < ddi::kWMax; ++i) r.w[a][i] = static_cast<T>(H.wts[(q * 3 + a) * ddi::kWMax + i]);
-    }
-  }
-  ddi::NodeRec<T>* dn = nullptr;
-  HIP_TRY(upload(&dn, recs.data(), recs.size(), s, bytes), "upload node table");
-  P.nodes = dn;
   std::vector<double> cs(H.M), cs_half(H.M);
   for (int64_t q = 0; q < H.M; ++q) cs[q] = H.c[q] * H.cell;
   HIP_TRY(upload(&P.c_scaled, cs.data(), cs.size(), s, bytes), "upload weights");
@@ -93,9 +87,25 @@ ddi_status build_device(ddi::DevicePlan& P, hipStream_t s, std::vector<ddi::Node
     const std::vector<double> ones(std::max(H.N[0], std::max(H.N[1], H.N[2])), 1.0);
     HIP_TRY(upload(&P.ones, ones.data(), ones.size(), s, bytes), "upload unit factors");
   }
-  // tile-owned interpolation (FP64 in 3D) and the weight rows of the matrix-core kernels
-  const bool tile_interp = ddi::interp_is_tiled(H, sizeof(T) == 8);
+  size_t nentries = 0;                       // interpolation partial sums (by rings)
+  int32_t nslots = 0;
+  const bool by_rings = ddi::interp_by_rings(H, sizeof(T) == 8);
   const bool use_pads = ddi::uses_weight_rows(H);
+  // (with matrix-core spread and interpolation by rings no kernel reads the node records)
+  if (!(by_rings && use_pads)) {
+    recs.resize(H.M);
+    for (int64_t q = 0; q < H.M; ++q) {
+      ddi::NodeRec<T>& r = recs[q];
+      std::memset(&r, 0, sizeof(r));
+      for (int a = 0; a < 3; ++a) {
+        r.l0[a] = H.l0[3 * q + a];
+        for (int i = 0; i < ddi::kWMax; ++i) r.w[a][i] = static_cast<T>(H.wts[(q * 3 + a) * ddi::kWMax + i]);
+      }
+    }
+    ddi::NodeRec<T>* dn = nullptr;
+    HIP_TRY(upload(&dn, recs.data(), recs.size(), s, bytes), "upload node table");
+    P.nodes = dn;
+  }
   for (int w = 0; w < 2; ++w) {
     const ddi::Schedule& S = H.sched[w];
     auto& D = P.dsched[w];
@@ -105,21 +115,39 @@ ddi_status build_device(ddi::DevicePlan& P, hipStream_t s, std::vector<ddi::Node
     HIP_TRY(upload(&D.interp_items, S.interp_items.data(), S.interp_items.size(), s, bytes), "upload interp groups");
     HIP_TRY(upload(&D.interp_direct, S.interp_direct.data(), S.interp_direct.size(), s, bytes),
             "upload interp list");
-    if (tile_interp) {
-      HIP_TRY(upload(&D.gptr, S.gptr.data(), S.gptr.size(), s, bytes), "upload interp gather");
-      HIP_TRY(upload(&D.gpos, S.gpos.data(), S.gpos.size(), s, bytes), "upload interp gather");
-    }
     if (use_pads) HIP_TRY(upload(&D.ent, S.ent.data(), S.ent.size(), s, bytes), "upload entry table");
+    nslots = std::max(nslots, S.nslots);
+    if (!by_rings) continue;
+    const ddi::RingSchedule& R = rings.sched[w];
+    auto& Q = P.drings[w];
+    HIP_TRY(upload(&Q.refs, R.refs.data(), R.refs.size(), s, bytes), "upload ring references");
+    HIP_TRY(upload(&Q.ent, R.ent.data(), R.ent.size(), s, bytes), "upload ring entries");
+    HIP_TRY(upload(&Q.interp, R.interp.data(), R.interp.size(), s, bytes), "upload interpolation items");
+    HIP_TRY(upload(&Q.interp_cut, R.interp_cut.data(), R.interp_cut.size(), s, bytes), "upload interpolation regions");
+    HIP_TRY(upload(&Q.gptr, R.gptr.data(), R.gptr.size(), s, bytes), "upload interp gather");
+    HIP_TRY(upload(&Q.gpos, R.gpos.data(), R.gpos.size(), s, bytes), "upload interp gather");
+    // workgroup b takes item b / 8 of the region of XCD b mod 8
+    int longest = 0;
+    for (size_t x = 0; x + 1 < R.interp_cut.size(); ++x) longest = std::max(longest, R.interp_cut[x + 1] - R.interp_cut[x]);
+    Q.ninterp = 8 * longest;
+    nentries = std::max(nentries, R.ent.size() / 2);
   }
   if (use_pads) {
-    padrows.assign(static_cast<size_t>(H.M + 1) * 3 * ddi::kRowLen, T(0));   // + the zero record
+    rows.assign(static_cast<size_t>(H.M + 1) * 3 * ddi::kRowLen, T(0));   // + the zero record
     for (int64_t q = 0; q < H.M; ++q)
       for (int a = 0; a < 3; ++a)
         for (int i = 0; i < ddi::kWMax; ++i)
-          padrows[(q * 3 + a) * ddi::kRowLen + i] = static_cast<T>(H.wts[(q * 3 + a) * ddi::kWMax + i]);
+          rows[(q * 3 + a) * ddi::kRowLen + i] = static_cast<T>(H.wts[(q * 3 + a) * ddi::kWMax + i]);
     T* dp = nullptr;
-    HIP_TRY(upload(&dp, padrows.data(), padrows.size(), s, bytes), "upload weight rows");
+    HIP_TRY(upload(&dp, rows.data(), rows.size(), s, bytes), "upload weight rows");
     P.pads = dp;
+  }
+  if (by_rings) {
+    xyw.resize(static_cast<size_t>(H.M) * 2 * ddi::kWMax);
+    for (int64_t q = 0; q < H.M; ++q)
+      std::memcpy(&xyw[q * 2 * ddi::kWMax], &H.wts[q * 3 * ddi::kWMax], 2 * ddi::kWMax * sizeof(double));
+    HIP_TRY(upload(&P.xyw, xyw.data(), xyw.size(), s, bytes), "upload ring weight rows");
+    HIP_TRY(upload(&P.ring_wz, rings.wz.data(), rings.wz.size(), s, bytes), "upload ring weights");
   }
   // twiddles for every FFT length used: fine grid sizes and the unpadded sizes
   tws.assign(ddi::kTwSlots, {});
@@ -150,13 +178,11 @@ ddi_status build_device(ddi::DevicePlan& P, hipStream_t s, std::vector<ddi::Node
   }
   HIP_TRY(hipMalloc(&P.gnodes, H.M * sizeof(ddi::Complex<T>)), "allocate node values");
   bytes += H.M * static_cast<int64_t>(sizeof(ddi::Complex<T>));
-  const size_t nentries = std::max(H.sched[0].list.size(), H.sched[1].list.size());
-  if (nentries > 0 && tile_interp) {
+  if (nentries > 0) {
     const int64_t ib = static_cast<int64_t>(nentries) * sizeof(ddi::Complex<double>);
     HIP_TRY(hipMalloc(&P.ipartial, ib), "allocate interpolation partial sums");
     bytes += ib;
   }
-  const int32_t nslots = std::max(H.sched[0].nslots, H.sched[1].nslots);
   if (nslots > 0) {
     const int64_t pbytes = static_cast<int64_t>(nslots) * 64 * ddi::kTileZ * sizeof(ddi::Complex<T>);
     HIP_TRY(hipMalloc(&P.partial, pbytes), "allocate spread partial tiles");
@@ -270,8 +296,14 @@ ddi_status ddi_plan(const ddi_params* params, void* stream, ddi_plan_t* out) {
   ddi::DevicePlan& P = plan->P;
   int st = DDI_OK;
   std::string msg;
+  ddi::RingTables rings;
   try {
-    msg = ddi::build_tables(*params, P.H, &st);
+    const bool by_rings = params->dim == 3 && params->prec == DDI_FP64;
+    msg = ddi::build_tables(*params, P.H, &st, !by_rings);
+    if (st == DDI_OK && by_rings) {
+      msg = ddi::build_rings(P.H, static_cast<int>(params->n_pol), rings);
+      if (!msg.empty()) st = DDI_ENOTSUP;
+    }
   } catch (const std::bad_alloc&) {
     delete plan;
     return fail(DDI_ENOMEM, "host allocation failed while building plan tables");
@@ -289,7 +321,7 @@ ddi_status ddi_plan(const ddi_params* params, void* stream, ddi_plan_t* out) {
     return fail(DDI_EDEVICE, "no HIP device");
   }
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  {
+  if (!ddi::interp_by_rings(P.H, !P.mixed)) {
     // grouped interpolation stages its region in LDS; without room for it, every node goes direct
     int max_lds = 0;
     if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, P.device) != hipSuccess) max_lds = 0;
@@ -310,8 +342,10 @@ ddi_status ddi_plan(const ddi_params* params, void* stream, ddi_plan_t* out) {
   std::vector<std::vector<ddi::Complex<float>>> tf;
   std::vector<double> pd;
   std::vector<float> pf;
+  std::vector<double> xyw;
   try {
-    ds = P.mixed ? build_device<float>(P, s, rf, tf, pf) : build_device<double>(P, s, rd, td, pd);
+    ds = P.mixed ? build_device<float>(P, s, rings, rf, tf, pf, xyw)
+                 : build_device<double>(P, s, rings, rd, td, pd, xyw);
   } catch (const std::bad_alloc&) {
     ds = fail(DDI_ENOMEM, "host allocation failed while uploading plan tables");
   }

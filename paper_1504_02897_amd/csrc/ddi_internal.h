@@ -37,9 +37,6 @@ constexpr int kSpreadBatch = DDI_SPREAD_BATCH;
 // spread: a tile with more nodes is split into chunks of this many (partial tiles + reduce);
 // the matrix-core kernels take longer chunks (cheaper per node)
 constexpr int kSpreadChunk = DDI_SPREAD_CHUNK;
-#ifndef DDI_INTERP_BREG
-#define DDI_INTERP_BREG 1      // the interpolation's tile fragments held in registers across blocks
-#endif
 #ifndef DDI_SPREAD_CHUNK_2D
 #define DDI_SPREAD_CHUNK_2D 32
 #endif
@@ -60,18 +57,6 @@ constexpr int kSpreadWaves = DDI_SPREAD_WAVES;
 constexpr int kRowLen = kWMax;    // weight row of the matrix-core kernels: w weights, then zeros
 constexpr int kOffBias = 8;       // entry offsets are stored biased by this (non-negative bytes)
 constexpr int kEntPad = 32;       // zero entries after the last one (blocks of 16 may read past an item)
-#ifndef DDI_INTERP_TILE
-#define DDI_INTERP_TILE 1
-#endif
-// FP64 interpolation in 3D: 1 = tile-owned (each fine-grid tile read once by a wave whose
-// lanes are (tile, node) entries; one partial per entry, gathered per node); 0 = node-owned
-// (LDS-staged groups plus direct reads of the fine grid), which FP32 and 2D always use
-constexpr bool kInterpTile = DDI_INTERP_TILE != 0;
-#ifndef DDI_INTERP_MFMA
-#define DDI_INTERP_MFMA 1
-#endif
-// tile-owned FP64 interpolation on the matrix cores where the plan has row windows
-constexpr bool kInterpMfma = DDI_INTERP_MFMA != 0;
 #ifndef DDI_SPREAD_MFMA
 #define DDI_SPREAD_MFMA 1
 #endif
@@ -113,6 +98,48 @@ struct ReduceItem {
   int32_t first_slot;
   int32_t nslots;
   int32_t pad;
+};
+
+// Ring schedule of the FP64 3D interpolation (rings.cpp, rings.hip).
+constexpr int kRingSpan = 32;      // last-axis positions that one interpolation block covers
+// Entries of an interpolation block (one ring may hold more): its rounds of 32 run one after the
+// other, and the blocks around k = 0 would last far longer than the others (32^3: 12.5 us with 512,
+// 7.1 with 128).
+constexpr int kRingInterpEntries = 128;
+// A ring met by a column: its last-axis origin relative to the window, and its entries over the
+// column ent[start, start + count).
+struct RingRef {
+  int32_t ring;
+  int32_t zr;
+  int32_t ent;
+  int32_t count;
+};
+// A block of ring work: references [ref0, ref0 + nref) of column col, with the nent entries from
+// ent0, over the last-axis positions [zs, zs + 4 ks) of the window.
+struct RingItem {
+  int32_t col;
+  int32_t ref0;
+  int32_t nref;
+  int32_t zs;
+  int32_t ent0;
+  int32_t nent;
+  int32_t ks;
+  int32_t pad;
+};
+struct RingSchedule {
+  std::vector<RingRef> refs;
+  std::vector<int32_t> ent;        // per entry: node; (kOffBias + column origin - support origin) per axis
+                                   // as bytes x | y << 8, and the reference's
+                                   // place in its interpolation block << 16
+  std::vector<int32_t> col_ref;    // references of column c: [col_ref[c], col_ref[c + 1])
+  std::vector<RingItem> interp;
+  std::vector<int32_t> interp_cut; // XCD x takes the items [cut[x], cut[x + 1])
+  std::vector<int32_t> gptr, gpos; // per node, the entries whose partials make its value
+};
+struct HostTables;
+struct RingTables {
+  std::vector<double> wz;          // [rings][kWMax]: last-axis weights
+  RingSchedule sched[2];
 };
 
 // Interpolation and spread work lists over one subset of the nodes.
@@ -192,13 +219,19 @@ struct HostTables {
   double mv[3] = {0, 0, 1};
 };
 
-// Kernel selection shared by the plan upload and the drivers.
-inline bool uses_weight_rows(const HostTables& H) { return H.row_windows && ((kInterpTile && kInterpMfma) || kSpreadMfma); }
-// (FP64 only: for the FP32 plans' narrower kernel the node-owned interpolation measured faster)
-inline bool interp_is_tiled(const HostTables& H, bool fp64) { return kInterpTile && H.tile[0] == 8 && fp64; }
+// Kernel selection shared by the plan upload and the drivers.  FP64 in 3D interpolates by rings, FP32 in
+// 3D node by node: its narrower kernel leaves few nodes of a ring over a column (256^3, w = 8: 291 + 11
+// us by rings against 248; 128^3: 51 + 6 against 60).
+inline bool interp_by_rings(const HostTables& H, bool fp64) { return H.dim == 3 && fp64; }
+inline bool uses_weight_rows(const HostTables& H) { return H.row_windows && kSpreadMfma; }
 
 // Builds every host table of a plan.  Returns an empty string on success or an error message.
-std::string build_tables(const ddi_params& p, HostTables& t, int* status);
+// interp_lists = false leaves out the node-owned interpolation's groups and the per-node entry lists,
+// which the interpolation by rings does not use.
+std::string build_tables(const ddi_params& p, HostTables& t, int* status, bool interp_lists = true);
+
+// Builds the ring schedules of a 3D plan from its tables (npol = polar nodes of the rule).
+std::string build_rings(const HostTables& t, int npol, RingTables& out);
 
 // Accurate e^{-2 pi i k / n}, k in [0, n), interleaved (re, im).
 std::vector<double> twiddle_table(int n);
@@ -265,10 +298,20 @@ struct DevicePlan {
     ReduceItem* reduces = nullptr;
     InterpItem* interp_items = nullptr;
     int32_t* interp_direct = nullptr;
-    int32_t* gptr = nullptr;
-    int32_t* gpos = nullptr;
     int32_t* ent = nullptr;
   } dsched[2];
+  // FP64 in 3D: ring schedules (rings.hip)
+  struct DevRings {
+    RingRef* refs = nullptr;
+    int32_t* ent = nullptr;
+    RingItem* interp = nullptr;
+    int32_t* interp_cut = nullptr;
+    int32_t* gptr = nullptr;
+    int32_t* gpos = nullptr;
+    int ninterp = 0;             // workgroups
+  } drings[2];
+  double* ring_wz = nullptr;     // [rings][kWMax]
+  double* xyw = nullptr;         // [M][2][kWMax]: weight rows of axes 0 and 1
   bool interp_lds_ready = false;
   void* twiddles[kTwSlots] = {}; // per FFT length n (slot tw_slot(n) of fft.h): Complex<T>[n]
   // workspace
@@ -303,6 +346,8 @@ hipError_t run_set_dipole(DevicePlan& P, const double* n, const double* m, hipSt
 // The operator of the plan: run_apply, plus I_1 for a split plan (I_1 is its own transpose).
 template <typename T>
 hipError_t run_ddi(DevicePlan& P, const T* rho, T* phi, int sign, hipStream_t s, hipEvent_t* ev);
+// Interpolation at the nodes times scale, by rings (rings.hip).
+hipError_t ring_interp(DevicePlan& P, int which, Complex<double>* out, const double* scale, double sscalar, hipStream_t s);
 constexpr int kStages = 9;
 template <typename T>
 hipError_t run_gpe_energy_grad(DevicePlan& P, const GpeWork& W, const gpe_params& gp, const Complex<T>* psi,

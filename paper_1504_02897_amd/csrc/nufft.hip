@@ -567,246 +567,7 @@ __global__ void __launch_bounds__(64, 4) k_spread_mfma(C<T>* __restrict__ F, C<T
   }
 }
 
-// ------------------------------------------------------------------ tile-owned interpolation
-__device__ inline int mod_fine(int d, int n) { return d < 0 ? d + n : d; }
-
-// Lane-per-entry form (3D, 8 x 8 x kTileZ tiles): lane e of the wave takes entry e of the
-// tile (64 at a time), holds the node's kernel weights at the tile's positions in registers,
-// and walks the tile's 64 columns.  The tile is staged in LDS once per item (lane c loads
-// column c, coalesced along the last axis); every lane then reads the same column, so each
-// LDS read is a broadcast.  Per column a lane sums over z, then weights by y; per x row by x.
-// No cross-lane reduction.  Arithmetic in FP64.
-template <typename T>
-__global__ void __launch_bounds__(64) k_interp_col(const C<T>* __restrict__ F, const NodeRec<T>* __restrict__ nodes,
-                                                   const int32_t* __restrict__ list,
-                                                   const SpreadItem* __restrict__ items, int nf0, int nf1, int nf2,
-                                                   int nt1, int nt2, int w0, int w1, int w2,
-                                                   C<double>* __restrict__ part) {
-  constexpr int TX = 8, TY = 8, TZ = kTileZ;
-  const int lane = threadIdx.x;
-  const SpreadItem it = items[blockIdx.x];
-  if (it.tile < 0 || it.count == 0) return;  // padding item or empty tile
-  const int tz = it.tile % nt2;
-  const int ty = (it.tile / nt2) % nt1;
-  const int tx = it.tile / (nt2 * nt1);
-  const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
-  __shared__ C<T> tileF[TX * TY * TZ];       // [x][y][z]
-  {
-    const C<T>* row = F + (static_cast<int64_t>(x0 + lane / TY) * nf1 + (y0 + lane % TY)) * nf2 + z0;
-    C<T> v[TZ];
-#pragma unroll
-    for (int z = 0; z < TZ; ++z) v[z] = row[z];
-#pragma unroll
-    for (int z = 0; z < TZ; ++z) tileF[lane * TZ + z] = v[z];
-  }
-  __syncthreads();
-  for (int base = 0; base < it.count; base += 64) {
-    const int e = base + lane;
-    const bool valid = e < it.count;
-    const int q = list[it.start + (valid ? e : 0)];
-    const NodeRec<T>* nd = nodes + q;
-    // weight of tile position i on an axis: support index (tile origin + i - support origin)
-    // mod n_fine, zero outside [0, w); i < tile extent <= n_fine, so one subtraction reduces
-    auto weight = [&](int d0, int i, int n, int w, int a) {
-      int d = d0 + i;
-      if (d >= n) d -= n;
-      const bool in = valid && d < w;
-      const T v = nd->w[a][in ? d : 0];
-      return in ? static_cast<double>(v) : 0.0;
-    };
-    const int dx = mod_fine(x0 - nd->l0[0], nf0);
-    const int dy = mod_fine(y0 - nd->l0[1], nf1);
-    const int dz = mod_fine(z0 - nd->l0[2], nf2);
-    double wx[TX], wy[TY], wz[TZ];
-#pragma unroll
-    for (int i = 0; i < TX; ++i) wx[i] = weight(dx, i, nf0, w0, 0);
-#pragma unroll
-    for (int i = 0; i < TY; ++i) wy[i] = weight(dy, i, nf1, w1, 1);
-#pragma unroll
-    for (int i = 0; i < TZ; ++i) wz[i] = weight(dz, i, nf2, w2, 2);
-    double ar = 0.0, ai = 0.0;
-    for (int x = 0; x < TX; ++x) {
-      const C<T>* plane = tileF + x * TY * TZ;
-      double tr = 0.0, ti = 0.0;
-#pragma unroll
-      for (int y = 0; y < TY; ++y) {
-        const C<T>* col = plane + y * TZ;
-        double sr = 0.0, si = 0.0;
-#pragma unroll
-        for (int z = 0; z < TZ; ++z) {
-          const C<T> f = col[z];
-          sr += wz[z] * static_cast<double>(f.re);
-          si += wz[z] * static_cast<double>(f.im);
-        }
-        tr += wy[y] * sr;
-        ti += wy[y] * si;
-      }
-      ar += wx[x] * tr;
-      ai += wx[x] * ti;
-    }
-    if (valid) part[static_cast<int64_t>(it.start) + e] = C<double>{ar, ai};
-  }
-}
-
-// Matrix-core form of the same tile interpolation (FP64, 3D, weight rows).  For the
-// entries of a tile the partials are a dense product followed by a short weighting:
-//   G[e][(x,p)] = sum_{(y,z)} A[e][(y,z)] B[(y,z)][(x,p)],  A[e][(y,z)] = wy_e[y] wz_e[z],
-//   B[(y,z)][(x,p)] = part p (re, im) of F[x][y][z],           partial_e,p = sum_x wx_e[x] G[e][(x,p)].
-// v_mfma_f64_16x16x4f64 takes A[i][k] from lane i + 16k, B[k][j] from lane j + 16k and
-// leaves D[i][j] in lane j + 16 (i % 4), item i / 4.  Rows are entries (16 per block), the
-// 16 columns are (x, p), and K = (y, z) runs over 16 steps of 4: at step s lane group k
-// covers y = 4 (k / 2) + s / 4, z = 4 (k % 2) + s % 4, so a lane needs four y and four z
-// weights of its entry.  B is staged in LDS once per item in fragment order (each lane reads
-// its own element); the weights of a row block are loaded cooperatively (eight lanes per
-// contiguous run of a weight row) and published through LDS, their loads pipelined across
-// the blocks' matrix products.
-typedef double dbl4 __attribute__((ext_vector_type(4)));
-
-template <typename T>
-__global__ void __launch_bounds__(64) k_interp_mfma(const C<T>* __restrict__ F, const T* __restrict__ pads,
-                                                    const int2* __restrict__ ent,
-                                                    const SpreadItem* __restrict__ items, int nf1, int nf2, int nt1,
-                                                    int nt2, int64_t ent_bytes, int64_t rows_bytes, unsigned zrec,
-                                                    C<double>* __restrict__ part) {
-  const int lane = threadIdx.x;
-  const SpreadItem it = items[blockIdx.x];
-  if (it.tile < 0 || it.count == 0) return;  // padding item or empty tile
-  const int tz = it.tile % nt2;
-  const int ty = (it.tile / nt2) % nt1;
-  const int tx = it.tile / (nt2 * nt1);
-  constexpr int SB = 65;                     // fragment step stride (one pad: conflict-free staging)
-  __shared__ double fragB[16 * SB];
-  __shared__ double wts[16 * 24];            // [entry of the block][axis][8 tile positions]
-  const int nmb = (it.count + 15) / 16;
-  // Weights of a row block are loaded cooperatively (CoopLanes).  Entries past the item's
-  // count only fill rows of the product whose results are not stored.  The two dependent
-  // loads are pipelined across blocks: entry records two blocks ahead, weight rows one ahead.
-  const CoopLanes cl(lane);
-  const __amdgpu_buffer_rsrc_t ent_r = raw_buffer(ent, ent_bytes), rows_r = raw_buffer(pads, rows_bytes);
-  auto load_ent = [&](int mb, int2* en) { cl.entries(ent_r, (it.start + 16 * mb) * static_cast<int>(sizeof(int2)), en); };
-  auto load_rows = [&](const int2* en, double* raw) {
-#pragma unroll
-    for (int j = 0; j < 6; ++j) raw[j] = row_load<T>(rows_r, cl.row_offset<T>(en, j, zrec));
-  };
-  int2 en_a[2], en_b[2];
-  double raw[6];
-  load_ent(0, en_a);
-  if (nmb > 1) load_ent(1, en_b);
-  {
-    // the tile, eight lanes per 128-byte row: load r covers the row (x, y) = (r, lane / 8)
-    const int cy = lane >> 3, z = lane & 7;
-    const unsigned lo = static_cast<unsigned>(cy * nf2 + z);
-    const int at = (4 * (cy & 3) + (z & 3)) * SB + (2 * (cy >> 2) + (z >> 2)) * 16;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const C<T>* row = F + (static_cast<int64_t>(tx * 8 + r) * nf1 + ty * 8) * nf2 + tz * kTileZ;
-      const C<T> v = row[lo];
-      fragB[at + 2 * r] = static_cast<double>(v.re);
-      fragB[at + 2 * r + 1] = static_cast<double>(v.im);
-    }
-  }
-  load_rows(en_a, raw);
-#pragma unroll
-  for (int j = 0; j < 6; ++j) wts[cl.wslot(j)] = raw[j];
-  __syncthreads();
-  const int kk = lane >> 4, col = lane & 15, xo = col >> 1;
-  const int yo = 4 * (kk >> 1), zo = 4 * (kk & 1);
-  const bool b3 = (lane & 8) != 0, b2 = (lane & 4) != 0;
-#if DDI_INTERP_BREG
-  double bfr[16];                            // the lane's B fragments, the same for every block
-#pragma unroll
-  for (int st = 0; st < 16; ++st) bfr[st] = fragB[st * SB + lane];
-#endif
-  for (int mb = 0; mb < nmb; ++mb) {
-    double wy[4], wz[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      wy[i] = wts[col * 24 + 8 + yo + i];
-      wz[i] = wts[col * 24 + 16 + zo + i];
-    }
-    const double wxa = wts[col * 24 + 2 * kk], wxb = wts[col * 24 + 2 * kk + 1];
-    // en_b holds block mb + 1's entry records: start its rows, and block mb + 2's records
-    const bool more = mb + 1 < nmb;
-    if (more) {
-      load_rows(en_b, raw);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) en_a[j] = en_b[j];
-      if (mb + 2 < nmb) load_ent(mb + 2, en_b);
-    }
-    dbl4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int st = 0; st < 16; ++st)
-#if DDI_INTERP_BREG
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(wy[st >> 2] * wz[st & 3], bfr[st], acc, 0, 0, 0);
-#else
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(wy[st >> 2] * wz[st & 3], fragB[st * SB + lane], acc, 0, 0, 0);
-#endif
-    // item i holds row 4 i + kk (entry 16 mb + 4 i + kk), an A row of lane (4 i + kk) + 16 (xo / 2)
-    double v[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int src = (4 * i + kk) + 16 * (xo >> 1);
-      const double xa = __shfl(wxa, src, 64), xb = __shfl(wxb, src, 64);
-      v[i] = acc[i] * ((xo & 1) ? xb : xa);
-    }
-    // sum over x (lane bits 1..3) for the four items at once: exchange halves across bit 3,
-    // then bit 2, then add across bit 1; the lane ends with item b2 + 2 b3
-    double u[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const double send = b3 ? v[j] : v[j + 2], keep = b3 ? v[j + 2] : v[j];
-      u[j] = keep + __shfl_xor(send, 8, 64);
-    }
-    double r;
-    {
-      const double send = b2 ? u[0] : u[1], keep = b2 ? u[1] : u[0];
-      r = keep + __shfl_xor(send, 4, 64);
-    }
-    r += __shfl_xor(r, 2, 64);
-    const int er = 4 * ((b2 ? 1 : 0) + (b3 ? 2 : 0)) + kk;   // entry of the block
-    if ((lane & 2) == 0 && 16 * mb + er < it.count)
-      reinterpret_cast<double*>(part + (static_cast<int64_t>(it.start) + 16 * mb))[2 * er + (lane & 1)] = r;
-    if (more) {
-      __syncthreads();                       // every lane has read this block's weights
-#pragma unroll
-      for (int j = 0; j < 6; ++j) wts[cl.wslot(j)] = raw[j];
-      __syncthreads();
-    }
-  }
-}
-
-// Sum the partials of each node (its list positions, in list order) and apply the node scale.
-template <typename T>
-__global__ void __launch_bounds__(256) k_interp_gather(const C<double>* __restrict__ part,
-                                                       const int32_t* __restrict__ gptr,
-                                                       const int32_t* __restrict__ gpos, int64_t M,
-                                                       const double* __restrict__ scale, double sscalar,
-                                                       C<T>* __restrict__ out) {
-  const int64_t q = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (q >= M) return;
-  const int b = gptr[q], e = gptr[q + 1];
-  if (b == e) return;                        // node outside the scheduled set
-  // eight entries per round, all loads in flight, summed in list order
-  double sr = 0.0, si = 0.0;
-  for (int j0 = b; j0 < e; j0 += 8) {
-    int pos[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) pos[j] = gpos[j0 + j < e ? j0 + j : b];
-    C<double> v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = part[pos[j]];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      if (j0 + j < e) {
-        sr += v[j].re;
-        si += v[j].im;
-      }
-    }
-  }
-  const double s = scale ? scale[q] * sscalar : sscalar;
-  out[q] = C<T>{static_cast<T>(s * sr), static_cast<T>(s * si)};
-}
-
+// ------------------------------------------------------------------ reduce of split tiles
 // Sum the partial tiles of each split tile (deterministic): kReduceSplit workgroups per tile
 // (a hot tile's slots are then read by several CUs), each taking a part of the tile's points
 // with kReduceGroups threads per point; thread group u sums the slots u, u + G, u + 2G, ... in
@@ -986,41 +747,16 @@ template <typename T, int W>
 static hipError_t interp_d(DevicePlan& P, int which, C<T>* out, const double* scale, double sscalar,
                            hipStream_t s) {
   if (P.H.W[0] == 1) return interp_w<T, 1, W, 8>(P, which, out, scale, sscalar, s);
-  return interp_w<T, W, W, kInterpBlock3>(P, which, out, scale, sscalar, s);
-}
-
-template <typename T>
-static hipError_t interp_tile_t(DevicePlan& P, int which, C<T>* out, const double* scale, double sscalar,
-                                hipStream_t s) {
-  const HostTables& H = P.H;
-  const Schedule& S = H.sched[which];
-  const DevicePlan::DevSchedule& D = P.dsched[which];
-  const int nitems = static_cast<int>(S.items.size());
-  if (nitems > 0 && !S.list.empty()) {
-    if (kInterpMfma && H.row_windows)
-      hipLaunchKernelGGL((k_interp_mfma<T>), dim3(nitems), dim3(64), 0, s, reinterpret_cast<const C<T>*>(P.fine),
-                         reinterpret_cast<const T*>(P.pads), reinterpret_cast<const int2*>(D.ent), D.items, H.nf[1],
-                         H.nf[2], H.ntiles[1], H.ntiles[2], ent_bytes(S), rows_bytes<T>(H), zero_record<T>(H),
-                         reinterpret_cast<C<double>*>(P.ipartial));
-    else
-      hipLaunchKernelGGL((k_interp_col<T>), dim3(nitems), dim3(64), 0, s, reinterpret_cast<const C<T>*>(P.fine),
-                         reinterpret_cast<const NodeRec<T>*>(P.nodes), D.list, D.items, H.nf[0], H.nf[1], H.nf[2],
-                         H.ntiles[1], H.ntiles[2], H.W[0], H.W[1], H.W[2], reinterpret_cast<C<double>*>(P.ipartial));
-    DDI_CHECK(hipGetLastError());
-  }
-  if (H.M > 0) {
-    const int blocks = static_cast<int>((H.M + 255) / 256);
-    hipLaunchKernelGGL((k_interp_gather<T>), dim3(blocks), dim3(256), 0, s,
-                       reinterpret_cast<const C<double>*>(P.ipartial), D.gptr, D.gpos, H.M, scale, sscalar, out);
-    DDI_CHECK(hipGetLastError());
-  }
-  return hipSuccess;
+  if constexpr (sizeof(T) == 4) return interp_w<T, W, W, kInterpBlock3>(P, which, out, scale, sscalar, s);
+  return hipErrorInvalidValue;               // (FP64 in 3D interpolates by rings)
 }
 
 template <typename T>
 static hipError_t interp(DevicePlan& P, int which, C<T>* out, const double* scale, double sscalar,
                          hipStream_t s) {
-  if (interp_is_tiled(P.H, sizeof(T) == 8)) return interp_tile_t<T>(P, which, out, scale, sscalar, s);
+  if constexpr (sizeof(T) == 8) {
+    if (interp_by_rings(P.H, true)) return ring_interp(P, which, out, scale, sscalar, s);
+  }
   {
     switch (P.H.w) {
       case 2: return interp_d<T, 2>(P, which, out, scale, sscalar, s);

@@ -163,25 +163,10 @@ std::string build_interp_schedule(const HostTables& t, const std::vector<uint64_
   return "";
 }
 
-// Spread work over the nodes selected by `used`: for every tile of the fine grid, the
-// selected nodes whose support meets it (tiles in Morton order); tiles with more than
-// `chunk` nodes are split into chunks whose partial tiles are summed by reduce items.
+// The last-axis and axis-1 windows of the nodes selected by `used`.
 template <typename Used>
-std::string build_spread_schedule(const HostTables& t, const std::vector<int64_t>& tile_order, Used used,
-                                  Schedule& S) {
+void build_windows(const HostTables& t, Used used, Schedule& S) {
   const int64_t M = t.M;
-  const int64_t ntile_total = static_cast<int64_t>(t.ntiles[0]) * t.ntiles[1] * t.ntiles[2];
-  auto touched = [&](int64_t s, int a, int* out) {
-    int cnt = 0;
-    for (int i = 0; i < t.W[a]; ++i) {
-      int pos = (t.l0[3 * s + a] + i) % t.nf[a];
-      int tl = pos / t.tile[a];
-      bool seen = false;
-      for (int j = 0; j < cnt; ++j) seen = seen || out[j] == tl;
-      if (!seen) out[cnt++] = tl;
-    }
-    return cnt;
-  };
   // last-axis window: the complement of the longest circular run of zalign-blocks that no
   // support touches (the whole axis when that run is empty or the axis is short)
   {
@@ -227,6 +212,27 @@ std::string build_spread_schedule(const HostTables& t, const std::vector<int64_t
       S.ny = std::min(n, 2 * half);
     }
   }
+}
+
+// Spread work over the nodes selected by `used`: for every tile of the fine grid, the
+// selected nodes whose support meets it (tiles in Morton order); tiles with more than
+// `chunk` nodes are split into chunks whose partial tiles are summed by reduce items.
+template <typename Used>
+std::string build_spread_schedule(const HostTables& t, const std::vector<int64_t>& tile_order, Used used,
+                                  bool interp_lists, Schedule& S) {
+  const int64_t M = t.M;
+  const int64_t ntile_total = static_cast<int64_t>(t.ntiles[0]) * t.ntiles[1] * t.ntiles[2];
+  auto touched = [&](int64_t s, int a, int* out) {
+    int cnt = 0;
+    for (int i = 0; i < t.W[a]; ++i) {
+      int pos = (t.l0[3 * s + a] + i) % t.nf[a];
+      int tl = pos / t.tile[a];
+      bool seen = false;
+      for (int j = 0; j < cnt; ++j) seen = seen || out[j] == tl;
+      if (!seen) out[cnt++] = tl;
+    }
+    return cnt;
+  };
   auto in_window = [&](int z) { return ((z - S.z0) % t.nf[2] + t.nf[2]) % t.nf[2] < S.nz; };
   std::vector<int64_t> count(ntile_total + 1, 0);
   int tx[kWMax], ty[kWMax], tz[kWMax];
@@ -325,6 +331,7 @@ std::string build_spread_schedule(const HostTables& t, const std::vector<int64_t
       }
     }
   }
+  if (!interp_lists) return "";
   // per node, the positions of its entries in the list (in list order)
   S.gptr.assign(M + 1, 0);
   for (int32_t q : S.list) S.gptr[q + 1]++;
@@ -349,7 +356,7 @@ std::vector<double> twiddle_table(int n) {
   return t;
 }
 
-std::string build_tables(const ddi_params& p, HostTables& t, int* status) {
+std::string build_tables(const ddi_params& p, HostTables& t, int* status, bool interp_lists) {
   *status = DDI_EINVAL;
   if (p.dim != 2 && p.dim != 3) return "dim must be 2 or 3";
   const int d = p.dim;
@@ -636,8 +643,10 @@ std::string build_tables(const ddi_params& p, HostTables& t, int* status) {
   for (int which = 0; which < 2; ++which) {
     Schedule& S = t.sched[which];
     auto used = [&](int64_t s2) { return which == kAll || t.half_factor[s2] > 0.0; };
-    std::string err = build_interp_schedule(t, key, used, S);
-    if (err.empty()) err = build_spread_schedule(t, tile_order, used, S);
+    build_windows(t, used, S);
+    std::string err;
+    if (interp_lists) err = build_interp_schedule(t, key, used, S);
+    if (err.empty()) err = build_spread_schedule(t, tile_order, used, interp_lists, S);
     if (!err.empty()) return err;
   }
   *status = DDI_OK;
