@@ -2,12 +2,10 @@
 //
 //   type-2 (grid -> nodes): deconvolve + zero-pad fused into the first FFT pass, pruned
 //     3-pass FFT on the oversampled grid, then interpolation at the quadrature nodes with the
-//     weights g_q = c_q prod(h) rhohat_q applied at the end.  FP64 interpolation in 3D is
-//     tile-owned: per 8 x 8 x 8 tile of the fine grid, the (tile, node) entries of the tile are
-//     contracted with the tile as FP64 matrix products (k_interp_mfma), one partial per entry,
-//     summed per node by a gather kernel (the fine grid is read once).  Otherwise interpolation
-//     is node-owned: nodes grouped by home block read an LDS-staged support region, the rest
-//     read the grid directly (one wave per four nodes, compile-time kernel width).
+//     weights g_q = c_q prod(h) rhohat_q applied at the end.  FP64 interpolation in 3D goes by rings
+//     (rings.hip).  Otherwise interpolation is node-owned: nodes grouped by home block read an
+//     LDS-staged support region, the rest read the grid directly (one wave per four nodes,
+//     compile-time kernel width).
 //   type-1 (nodes -> grid): tile-owned spread, no atomics.  In 3D a tile is accumulated in
 //     registers by FP64 matrix products over its entries (k_spread_mfma); in 2D a wave owns a
 //     tile and sums the nodes staged 64 at a time in LDS as tile-relative weight vectors.  Hot
