@@ -102,12 +102,13 @@ struct ReduceItem {
 
 // Ring schedule of the FP64 3D interpolation (rings.cpp, rings.hip).
 constexpr int kRingSpan = 32;      // last-axis positions that one interpolation block covers
-// Entries of an interpolation block (one ring may hold more): its rounds of 32 run one after the
-// other, and the blocks around k = 0 would last far longer than the others (32^3: 12.5 us with 512,
-// 7.1 with 128).
+// Most entries of an interpolation block: its rounds of 32 run one after the other, and the blocks around
+// k = 0 would last far longer than the others (32^3: 12.5 us with 512, 7.1 with 128).  A ring with more
+// nodes over a column is cut into several references (32^3, w = 4, a 4 x 4 x 4096 rule, with the gather:
+// 12 us, 67 with whole rings).
 constexpr int kRingInterpEntries = 128;
-// A ring met by a column: its last-axis origin relative to the window, and its entries over the
-// column ent[start, start + count).
+// A ring met by a column (or a part of one): its last-axis origin relative to the window, and its entries
+// over the column [ent, ent + count).
 struct RingRef {
   int32_t ring;
   int32_t zr;

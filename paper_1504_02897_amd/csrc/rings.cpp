@@ -80,9 +80,10 @@ std::string build_one(const HostTables& t, const std::vector<int32_t>& order, co
     for (int i = first; i <= last; ++i) out[c++] = i % t.ntiles[a];
     return c;
   };
-  // pass 0 counts, pass 1 fills: references and entries per column
+  // pass 0 counts, pass 1 fills: references and entries per column.  A ring with more than
+  // kRingInterpEntries nodes over a column (rules with many azimuthal nodes) gets several references.
   std::vector<int64_t> nref(ncol + 1, 0), nent(ncol + 1, 0);
-  std::vector<int32_t> seen(ncol, -1);
+  std::vector<int32_t> seen(ncol, -1), held(ncol, 0);   // last ring over the column, entries of its reference
   R.col_ref.assign(ncol + 1, 0);
   std::vector<int64_t> fref, fent;
   int stamp = 0;
@@ -103,45 +104,49 @@ std::string build_one(const HostTables& t, const std::vector<int32_t>& order, co
       fent.assign(nent.begin(), nent.end());
     }
     for (int r : byz) {
-        const int zr = zr_of(r);
-        ++stamp;
-        for (int i = rstart[r]; i < rstart[r + 1]; ++i) {
-          const int64_t q = rnode[i];
-          if (half && !(t.half_factor[q] > 0.0)) continue;
-          int tx[4], ty[4];
-          const int l0x = t.l0[3 * q], l0y = t.l0[3 * q + 1];
-          const int nx = tiles(l0x, 0, tx), ny = tiles(l0y, 1, ty);
-          for (int a = 0; a < nx; ++a)
-            for (int b = 0; b < ny; ++b) {
-              const int c = tx[a] * nt1 + ty[b];
-              if (pass == 0) {
-                if (seen[c] != stamp) { seen[c] = stamp; nref[c]++; }
-                nent[c]++;
-                continue;
-              }
-              if (seen[c] != stamp) {
-                seen[c] = stamp;
-                R.refs[fref[c]++] = RingRef{r, zr, static_cast<int32_t>(fent[c]), 0};
-              }
-              R.refs[fref[c] - 1].count++;
-              auto off = [&](int org, int l0, int ax) {
-                int d = org - l0;
-                if (d < 0) d += t.nf[ax];
-                if (d > t.nf[ax] - 8) d -= t.nf[ax];     // the column starts before the support
-                return d;
-              };
-              const int dx = off(tx[a] * 8, l0x, 0), dy = off(ty[b] * 8, l0y, 1);
-              if (dx < -7 || dx >= t.W[0] || dy < -7 || dy >= t.W[1]) return "ring entry outside its weight row";
-              R.ent[2 * fent[c]] = static_cast<int32_t>(q);
-              R.ent[2 * fent[c] + 1] = (kOffBias + dx) | (kOffBias + dy) << 8;
-              fent[c]++;
+      const int zr = zr_of(r);
+      ++stamp;
+      for (int i = rstart[r]; i < rstart[r + 1]; ++i) {
+        const int64_t q = rnode[i];
+        if (half && !(t.half_factor[q] > 0.0)) continue;
+        int tx[4], ty[4];
+        const int l0x = t.l0[3 * q], l0y = t.l0[3 * q + 1];
+        const int nx = tiles(l0x, 0, tx), ny = tiles(l0y, 1, ty);
+        for (int a = 0; a < nx; ++a)
+          for (int b = 0; b < ny; ++b) {
+            const int c = tx[a] * nt1 + ty[b];
+            const bool fresh = seen[c] != stamp || held[c] == kRingInterpEntries;
+            if (fresh) {
+              seen[c] = stamp;
+              held[c] = 0;
             }
-        }
+            ++held[c];
+            if (pass == 0) {
+              nref[c] += fresh;
+              nent[c]++;
+              continue;
+            }
+            if (fresh) R.refs[fref[c]++] = RingRef{r, zr, static_cast<int32_t>(fent[c]), 0};
+            R.refs[fref[c] - 1].count++;
+            auto off = [&](int org, int l0, int ax) {
+              int d = org - l0;
+              if (d < 0) d += t.nf[ax];
+              if (d > t.nf[ax] - 8) d -= t.nf[ax];     // the column starts before the support
+              return d;
+            };
+            const int dx = off(tx[a] * 8, l0x, 0), dy = off(ty[b] * 8, l0y, 1);
+            if (dx < -7 || dx >= t.W[0] || dy < -7 || dy >= t.W[1]) return "ring entry outside its weight row";
+            R.ent[2 * fent[c]] = static_cast<int32_t>(q);
+            R.ent[2 * fent[c] + 1] = (kOffBias + dx) | (kOffBias + dy) << 8;
+            fent[c]++;
+          }
+      }
     }
   }
   for (int c = 0; c <= ncol; ++c) R.col_ref[c] = static_cast<int32_t>(nref[c]);
-  // interpolation items: up to 16 rings of a column whose last-axis supports span at most
-  // kRingSpan positions; the block starts on a multiple of four positions (64 bytes of the grid)
+  // interpolation items: up to 16 references of a column whose last-axis supports span at most
+  // kRingSpan positions, with up to kRingInterpEntries entries; the block starts on a multiple of four
+  // positions (64 bytes of the grid)
   R.interp.clear();
   for (int c = 0; c < ncol; ++c) {
     int i = R.col_ref[c];
@@ -152,9 +157,9 @@ std::string build_one(const HostTables& t, const std::vector<int32_t>& order, co
       it.ref0 = i;
       it.zs = R.refs[i].zr & ~3;
       it.ent0 = R.refs[i].ent;
-            int n = 0;
+      int n = 0;
       while (i < e && n < 16 && R.refs[i].zr + w - it.zs <= kRingSpan &&
-             (n == 0 || it.nent + R.refs[i].count <= kRingInterpEntries)) {
+             it.nent + R.refs[i].count <= kRingInterpEntries) {
         for (int k = 0; k < R.refs[i].count; ++k) R.ent[2 * (R.refs[i].ent + k) + 1] |= n << 16;
         it.nent += R.refs[i].count;
         it.ks = (R.refs[i].zr + w - it.zs + 3) / 4;
