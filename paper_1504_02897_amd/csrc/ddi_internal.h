@@ -102,11 +102,14 @@ struct ReduceItem {
 
 // Ring schedule of the FP64 3D interpolation (rings.cpp, rings.hip).
 constexpr int kRingSpan = 32;      // last-axis positions that one interpolation block covers
-// Most entries of an interpolation block: its rounds of 32 run one after the other, and the blocks around
-// k = 0 would last far longer than the others (32^3: 12.5 us with 512, 7.1 with 128).  A ring with more
-// nodes over a column is cut into several references (32^3, w = 4, a 4 x 4 x 4096 rule, with the gather:
-// 12 us, 67 with whole rings).
+// Entries of an interpolation block: its rounds of 32 run one after the other, and the blocks around k = 0
+// would last far longer than the others (32^3: 12.5 us with 512, 7.1 with 128).  A ring with more nodes over
+// a column is cut into several references (32^3, w = 4, a 4 x 4 x 4096 rule, with the gather: 12 us, 67 with
+// whole rings), except where the entries make kRingBlocks longer blocks, which fill the chip several times
+// over: there a cut only repeats the ring's contraction (16^3, 6.1 M nodes, w = 14: 1157 us, 994 whole).
 constexpr int kRingInterpEntries = 128;
+constexpr int kRingMaxEntries = 1024;
+constexpr int kRingBlocks = 4096;
 // A ring met by a column (or a part of one): its last-axis origin relative to the window, and its entries
 // over the column [ent, ent + count).
 struct RingRef {

@@ -80,8 +80,17 @@ std::string build_one(const HostTables& t, const std::vector<int32_t>& order, co
     for (int i = first; i <= last; ++i) out[c++] = i % t.ntiles[a];
     return c;
   };
-  // pass 0 counts, pass 1 fills: references and entries per column.  A ring with more than
-  // kRingInterpEntries nodes over a column (rules with many azimuthal nodes) gets several references.
+  // A ring with more than `most` entries over a column (rules with many azimuthal nodes) gets several
+  // references: kRingInterpEntries, or more where blocks of that length would outnumber kRingBlocks
+  int64_t total = 0;
+  for (int r : byz)
+    for (int i = rstart[r]; i < rstart[r + 1]; ++i) {
+      const int64_t q = rnode[i];
+      if (half && !(t.half_factor[q] > 0.0)) continue;
+      total += ((t.l0[3 * q] % 8 + t.W[0] + 7) / 8) * ((t.l0[3 * q + 1] % 8 + t.W[1] + 7) / 8);
+    }
+  const int most = static_cast<int>(std::clamp<int64_t>(total / kRingBlocks, kRingInterpEntries, kRingMaxEntries));
+  // pass 0 counts, pass 1 fills: references and entries per column
   std::vector<int64_t> nref(ncol + 1, 0), nent(ncol + 1, 0);
   std::vector<int32_t> seen(ncol, -1), held(ncol, 0);   // last ring over the column, entries of its reference
   R.col_ref.assign(ncol + 1, 0);
@@ -115,7 +124,7 @@ std::string build_one(const HostTables& t, const std::vector<int32_t>& order, co
         for (int a = 0; a < nx; ++a)
           for (int b = 0; b < ny; ++b) {
             const int c = tx[a] * nt1 + ty[b];
-            const bool fresh = seen[c] != stamp || held[c] == kRingInterpEntries;
+            const bool fresh = seen[c] != stamp || held[c] == most;
             if (fresh) {
               seen[c] = stamp;
               held[c] = 0;
@@ -145,8 +154,8 @@ std::string build_one(const HostTables& t, const std::vector<int32_t>& order, co
   }
   for (int c = 0; c <= ncol; ++c) R.col_ref[c] = static_cast<int32_t>(nref[c]);
   // interpolation items: up to 16 references of a column whose last-axis supports span at most
-  // kRingSpan positions, with up to kRingInterpEntries entries; the block starts on a multiple of four
-  // positions (64 bytes of the grid)
+  // kRingSpan positions, with up to kRingInterpEntries entries (or one longer reference); the block
+  // starts on a multiple of four positions (64 bytes of the grid)
   R.interp.clear();
   for (int c = 0; c < ncol; ++c) {
     int i = R.col_ref[c];
@@ -159,7 +168,7 @@ std::string build_one(const HostTables& t, const std::vector<int32_t>& order, co
       it.ent0 = R.refs[i].ent;
       int n = 0;
       while (i < e && n < 16 && R.refs[i].zr + w - it.zs <= kRingSpan &&
-             it.nent + R.refs[i].count <= kRingInterpEntries) {
+             (n == 0 || it.nent + R.refs[i].count <= kRingInterpEntries)) {
         for (int k = 0; k < R.refs[i].count; ++k) R.ent[2 * (R.refs[i].ent + k) + 1] |= n << 16;
         it.nent += R.refs[i].count;
         it.ks = (R.refs[i].zr + w - it.zs + 3) / 4;

@@ -1,7 +1,8 @@
 """The blocks of the FP64 3D interpolation by rings.
 
-CPU: no block holds more entries than kRingInterpEntries (its rounds run one after the other), also where
-one ring has more than that over a column (rules with many azimuthal nodes), no block reaches beyond the
+CPU: no block of these plans holds more than 128 entries (its rounds run one after the other), also where one
+ring has more than that over a column (rules with many azimuthal nodes); where the entries make thousands of
+blocks the limit rises to entries / 4096, at most 1024.  No block reaches beyond the
 last-axis window, whose neighbourhood the transforms never write, and the blocks hold every (column, node)
 pair of the tile lists once at the right offsets, also for nodes beyond the Nyquist box."""
 import os
@@ -18,7 +19,7 @@ BLOCK_ENTRIES = 128
 PLANS = [((16, 16, 16), (5, 5, 400), 1e-13, 0, 1, True), ((32, 32, 32), (4, 4, 4096), 1e-7, 0, 1, True),
          ((16, 32, 24), (3, 4, 301), 1e-9, 0, 1, True), ((32, 32, 32), (9, 6, 257), 1e-15, 0, 0, True),
          ((64, 64, 64), (16, 13, 32), 1e-13, 1, 1, False), ((48, 16, 64), (31, 15, 34), 1e-11, 0, 1, False),
-         ((128, 128, 128), (1, 2, 128), 1e-15, 0, 1, False)]
+         ((128, 128, 128), (1, 2, 128), 1e-15, 0, 1, False), ((32, 32, 32), (40, 20, 400), 1e-13, 0, 1, True)]
 
 
 def build_driver(tmp_path_factory, name):
@@ -46,9 +47,9 @@ def test_no_block_is_longer_than_its_limit(blocks, n, quad, tol, split, mask, fu
     assert r.returncode == 0, r.stdout + r.stderr
     lines = [[int(v) for v in ln.split()] for ln in r.stdout.splitlines()]
     assert len(lines) == 2
-    for _, count, longest, over, outside, faults in lines:
+    for _, count, longest, over, outside, faults, entries in lines:
         assert count > 0 and outside == 0 and faults == 0
-        assert longest <= BLOCK_ENTRIES
+        assert longest <= min(max(entries // 4096, BLOCK_ENTRIES), 1024)
         assert (over > 0) == full
 
 
