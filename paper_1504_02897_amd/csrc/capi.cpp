@@ -73,7 +73,7 @@ void free_plan(ddi::DevicePlan& P) {
 template <typename T>
 ddi_status build_device(ddi::DevicePlan& P, hipStream_t s, const ddi::RingTables& rings,
                         std::vector<ddi::NodeRec<T>>& recs, std::vector<std::vector<ddi::Complex<T>>>& tws,
-                        std::vector<T>& rows, std::vector<double>& xyw) {
+                        std::vector<T>& rows) {
   const ddi::HostTables& H = P.H;
   int64_t& bytes = P.workspace_bytes;
   std::vector<double> cs(H.M), cs_half(H.M);
@@ -91,7 +91,7 @@ ddi_status build_device(ddi::DevicePlan& P, hipStream_t s, const ddi::RingTables
   int32_t nslots = 0;
   const bool by_rings = ddi::interp_by_rings(H, sizeof(T) == 8);
   const bool use_pads = ddi::uses_weight_rows(H);
-  // (with matrix-core spread and interpolation by rings no kernel reads the node records)
+  // (with matrix-core spread, interpolation by rings reads the weight rows and no kernel the node records)
   if (!(by_rings && use_pads)) {
     recs.resize(H.M);
     for (int64_t q = 0; q < H.M; ++q) {
@@ -141,14 +141,15 @@ ddi_status build_device(ddi::DevicePlan& P, hipStream_t s, const ddi::RingTables
     T* dp = nullptr;
     HIP_TRY(upload(&dp, rows.data(), rows.size(), s, bytes), "upload weight rows");
     P.pads = dp;
-  }
-  if (by_rings) {
-    xyw.resize(static_cast<size_t>(H.M) * 2 * ddi::kWMax);
+  } else if (by_rings) {
+    rows.resize(static_cast<size_t>(H.M) * 2 * ddi::kWMax);
     for (int64_t q = 0; q < H.M; ++q)
-      std::memcpy(&xyw[q * 2 * ddi::kWMax], &H.wts[q * 3 * ddi::kWMax], 2 * ddi::kWMax * sizeof(double));
-    HIP_TRY(upload(&P.xyw, xyw.data(), xyw.size(), s, bytes), "upload ring weight rows");
-    HIP_TRY(upload(&P.ring_wz, rings.wz.data(), rings.wz.size(), s, bytes), "upload ring weights");
+      std::copy_n(&H.wts[q * 3 * ddi::kWMax], 2 * ddi::kWMax, &rows[q * 2 * ddi::kWMax]);
+    T* dp = nullptr;
+    HIP_TRY(upload(&dp, rows.data(), rows.size(), s, bytes), "upload ring weight rows");
+    P.xyw = dp;
   }
+  if (by_rings) HIP_TRY(upload(&P.ring_wz, rings.wz.data(), rings.wz.size(), s, bytes), "upload ring weights");
   // twiddles for every FFT length used: fine grid sizes and the unpadded sizes
   tws.assign(ddi::kTwSlots, {});
   for (int a = 0; a < 3; ++a) {
@@ -342,10 +343,9 @@ ddi_status ddi_plan(const ddi_params* params, void* stream, ddi_plan_t* out) {
   std::vector<std::vector<ddi::Complex<float>>> tf;
   std::vector<double> pd;
   std::vector<float> pf;
-  std::vector<double> xyw;
   try {
-    ds = P.mixed ? build_device<float>(P, s, rings, rf, tf, pf, xyw)
-                 : build_device<double>(P, s, rings, rd, td, pd, xyw);
+    ds = P.mixed ? build_device<float>(P, s, rings, rf, tf, pf)
+                 : build_device<double>(P, s, rings, rd, td, pd);
   } catch (const std::bad_alloc&) {
     ds = fail(DDI_ENOMEM, "host allocation failed while uploading plan tables");
   }

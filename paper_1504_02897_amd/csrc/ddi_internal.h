@@ -315,7 +315,7 @@ struct DevicePlan {
     int ninterp = 0;             // workgroups
   } drings[2];
   double* ring_wz = nullptr;     // [rings][kWMax]
-  double* xyw = nullptr;         // [M][2][kWMax]: weight rows of axes 0 and 1
+  void* xyw = nullptr;           // T[M][2][kWMax]: weight rows of axes 0 and 1, without row windows
   bool interp_lds_ready = false;
   void* twiddles[kTwSlots] = {}; // per FFT length n (slot tw_slot(n) of fft.h): Complex<T>[n]
   // workspace

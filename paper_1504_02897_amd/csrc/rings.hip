@@ -68,7 +68,8 @@ constexpr int kRingKs = kRingSpan / 4;
 // for the column positions x = 2 v, 2 v + 1 (grid values loaded four lanes per 64-byte run and moved
 // to the lanes of the matrix fragment), then the four waves share the block's entries, eight lanes
 // each (lane u takes the row x = u).
-__global__ void __launch_bounds__(256, 6) k_ring_interp(const Cd* __restrict__ F, const double* __restrict__ xyw,
+__global__ void __launch_bounds__(256, 6) k_ring_interp(const Cd* __restrict__ F, const double* __restrict__ rows,
+                                                      int stride,
                                                       const double* __restrict__ wz, const int4* __restrict__ refs,
                                                       const RingItem* __restrict__ items,
                                                       const int32_t* __restrict__ cut, const int2* __restrict__ ent,
@@ -89,7 +90,7 @@ __global__ void __launch_bounds__(256, 6) k_ring_interp(const Cd* __restrict__ F
   auto load_ent = [&](int e) { e += 8 * v + e8; return ent[it.ent0 + (e < it.nent ? e : it.nent - 1)]; };
   auto load_w = [&](int2 r, double& x, double& y) {
     const int dx = (r.y & 255) - kOffBias + u, dy = ((r.y >> 8) & 255) - kOffBias + u;
-    const double* row = xyw + static_cast<int64_t>(r.x) * (2 * kWMax);
+    const double* row = rows + static_cast<int64_t>(r.x) * stride;
     x = static_cast<unsigned>(dx) < kWMax ? row[dx] : 0.0;
     y = static_cast<unsigned>(dy) < kWMax ? row[kWMax + dy] : 0.0;
   };
@@ -201,9 +202,15 @@ hipError_t ring_interp(DevicePlan& P, int which, Cd* out, const double* scale, d
   const HostTables& H = P.H;
   const DevicePlan::DevRings& D = P.drings[which];
   Cd* part = reinterpret_cast<Cd*>(P.ipartial);
+  // the weight rows of axes 0 and 1: the spread's where the plan has them, which then finds them in the
+  // Infinity Cache (with a copy of the two axes for this kernel alone the spread at 128^3 took 143 us
+  // instead of 139 at w = 14, 99 instead of 94 at w = 8), else a copy: the node records of 400 bytes
+  // straddle cache lines (16^3, 6.1 M nodes, w = 14: 1283 us against 991)
+  const double* rows = reinterpret_cast<const double*>(P.pads ? P.pads : P.xyw);
+  const int stride = P.pads ? 3 * kRowLen : 2 * kWMax;
   if (D.ninterp > 0) {
-    hipLaunchKernelGGL(k_ring_interp, dim3(D.ninterp), dim3(256), 0, s, reinterpret_cast<const Cd*>(P.fine), P.xyw,
-                       P.ring_wz, reinterpret_cast<const int4*>(D.refs), D.interp, D.interp_cut,
+    hipLaunchKernelGGL(k_ring_interp, dim3(D.ninterp), dim3(256), 0, s, reinterpret_cast<const Cd*>(P.fine), rows,
+                       stride, P.ring_wz, reinterpret_cast<const int4*>(D.refs), D.interp, D.interp_cut,
                        reinterpret_cast<const int2*>(D.ent), H.nf[1], H.nf[2], H.ntiles[1], H.sched[which].z0,
                        H.sched[which].nz, part);
     DDI_CHECK(hipGetLastError());
