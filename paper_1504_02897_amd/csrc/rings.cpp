@@ -197,17 +197,23 @@ std::string build_rings(const HostTables& t, int npol, RingTables& out) {
   const int64_t M = t.M;
   int nrad = 0;
   for (int64_t q = 0; q < M; ++q) nrad = std::max(nrad, t.index[3 * q] + 1);
-  // nodes by ring (counting sort: plan order inside a ring)
-  const int64_t nid = static_cast<int64_t>(nrad) * npol;
-  std::vector<int32_t> count(nid + 1, 0);
-  auto id = [&](int64_t q) { return static_cast<int64_t>(t.index[3 * q]) * npol + t.index[3 * q + 1]; };
-  for (int64_t q = 0; q < M; ++q) count[id(q) + 1]++;
-  for (int64_t i = 0; i < nid; ++i) count[i + 1] += count[i];
-  std::vector<int32_t> rnode(M), fill(count.begin(), count.end() - 1);
-  for (int64_t q = 0; q < M; ++q) rnode[fill[id(q)]++] = static_cast<int32_t>(q);
+  // nodes by ring, plan order inside a ring: two counting sorts, by polar, then by radial index (a table
+  // over all pairs would need memory for rings without a node)
+  std::vector<int32_t> rnode(M), other(M);
+  for (int64_t q = 0; q < M; ++q) other[q] = static_cast<int32_t>(q);
+  for (int a : {1, 0}) {
+    const std::vector<int32_t>& from = a == 1 ? other : rnode;
+    std::vector<int32_t>& to = a == 1 ? rnode : other;
+    std::vector<int32_t> start((a == 1 ? npol : nrad) + 1, 0);
+    for (int64_t q = 0; q < M; ++q) start[t.index[3 * q + a] + 1]++;
+    for (size_t i = 1; i < start.size(); ++i) start[i] += start[i - 1];
+    for (int32_t q : from) to[start[t.index[3 * static_cast<int64_t>(q) + a]]++] = q;
+  }
+  rnode.swap(other);
+  auto id = [&](int32_t q) { return std::make_pair(t.index[3 * static_cast<int64_t>(q)], t.index[3 * static_cast<int64_t>(q) + 1]); };
   std::vector<int32_t> rstart;               // the rings that hold a node
-  for (int64_t i = 0; i < nid; ++i)
-    if (count[i + 1] > count[i]) rstart.push_back(count[i]);
+  for (int64_t i = 0; i < M; ++i)
+    if (i == 0 || id(rnode[i]) != id(rnode[i - 1])) rstart.push_back(static_cast<int32_t>(i));
   const int nring = static_cast<int>(rstart.size());
   rstart.push_back(static_cast<int32_t>(M));
   out.wz.assign(static_cast<size_t>(nring) * kWMax, 0.0);

@@ -54,6 +54,16 @@ def test_no_block_is_longer_than_its_limit(blocks, n, quad, tol, split, mask, fu
 
 
 
+def test_rings_of_the_largest_rule_need_memory_for_its_nodes_only(tmp_path_factory):
+    """65536 x 65536 radial and polar nodes, four of them inside the box: 1 GiB of address space is plenty."""
+    exe = build_driver(tmp_path_factory, "ring_index")
+    r = subprocess.run(["bash", "-c", f"ulimit -v 1048576 && exec {exe}"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+    rings = [int(v) for v in r.stdout.split()]
+    # rings in the rule's order: (0, 65535) holds nodes 1 and 3, then (65535, 0) and (65535, 65535)
+    assert rings == [3, 2, 0, 1, 0]
+
+
 # ------------------------------------------------------------------ on the GPU
 def kernel_model(n, L, w, k):
     """The NUFFT's own model in 64 bits: per axis the deconvolution factors D and each node's kernel weights
