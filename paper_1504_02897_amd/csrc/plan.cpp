@@ -178,7 +178,8 @@ void build_windows(const HostTables& t, Used used, Schedule& S) {
       std::vector<char> hit(nb, 0);
       for (int64_t s = 0; s < M; ++s) {
         if (!used(s)) continue;
-        for (int i = 0; i < t.W[2]; ++i) hit[((t.l0[3 * s + 2] + i) % n) / za] = 1;
+        const int l0 = t.l0[3 * s + 2], last = (l0 + t.W[2] - 1) / za;
+        for (int i = l0 / za; i <= last; ++i) hit[i < nb ? i : i - nb] = 1;
       }
       int best = 0, best_end = 0;
       for (int i = 0, run = 0; i < 2 * nb; ++i) {   // twice round: runs that wrap
@@ -202,8 +203,10 @@ void build_windows(const HostTables& t, Used used, Schedule& S) {
       int need = 2;
       for (int64_t s = 0; s < M; ++s) {
         if (!used(s)) continue;
-        for (int i = 0; i < t.W[1]; ++i) {
-          const int pos = (t.l0[3 * s + 1] + i) % n;
+        // the outermost signed positions of a support are at its ends, or at n/2 where it comes past
+        const int l0 = t.l0[3 * s + 1], l1 = l0 + t.W[1] - 1;
+        for (int i : {l0, std::clamp(n / 2, l0, l1), l1}) {
+          const int pos = i < n ? i : i - n;
           const int sp = pos < n / 2 ? pos : pos - n;
           need = std::max(need, sp >= 0 ? 2 * (sp + 1) : -2 * sp);
         }
@@ -222,14 +225,13 @@ std::string build_spread_schedule(const HostTables& t, const std::vector<int64_t
                                   bool interp_lists, Schedule& S) {
   const int64_t M = t.M;
   const int64_t ntile_total = static_cast<int64_t>(t.ntiles[0]) * t.ntiles[1] * t.ntiles[2];
+  // tiles that a support meets on an axis, each once (on an axis of one tile it may come round to its first)
   auto touched = [&](int64_t s, int a, int* out) {
+    const int l0 = t.l0[3 * s + a], last = (l0 + t.W[a] - 1) / t.tile[a];
     int cnt = 0;
-    for (int i = 0; i < t.W[a]; ++i) {
-      int pos = (t.l0[3 * s + a] + i) % t.nf[a];
-      int tl = pos / t.tile[a];
-      bool seen = false;
-      for (int j = 0; j < cnt; ++j) seen = seen || out[j] == tl;
-      if (!seen) out[cnt++] = tl;
+    for (int i = l0 / t.tile[a]; i <= last; ++i) {
+      const int tl = i < t.ntiles[a] ? i : i - t.ntiles[a];
+      if (cnt == 0 || tl != out[0]) out[cnt++] = tl;
     }
     return cnt;
   };
@@ -320,7 +322,7 @@ std::string build_spread_schedule(const HostTables& t, const std::vector<int64_t
         const int32_t q = S.list[i];
         int32_t packed = 0;
         for (int a = 0; a < 3; ++a) {
-          int64_t d = (org[a] - t.l0[3 * q + a]) % t.nf[a];
+          int64_t d = org[a] - t.l0[3 * q + a];
           if (d < 0) d += t.nf[a];
           if (d > t.nf[a] - t.tile[a]) d -= t.nf[a];     // the tile starts before the support
           if (d < -(t.tile[a] - 1) || d > t.W[a] - 1) return "entry offset outside the weight row";
