@@ -109,7 +109,8 @@ ddi_status build_device(ddi::DevicePlan& P, hipStream_t s, const ddi::RingTables
   for (int w = 0; w < 2; ++w) {
     const ddi::Schedule& S = H.sched[w];
     auto& D = P.dsched[w];
-    HIP_TRY(upload(&D.list, S.list.data(), S.list.size(), s, bytes), "upload spread lists");
+    // (the matrix-core spread reads the entry table instead of the list)
+    if (!use_pads) HIP_TRY(upload(&D.list, S.list.data(), S.list.size(), s, bytes), "upload spread lists");
     HIP_TRY(upload(&D.items, S.items.data(), S.items.size(), s, bytes), "upload spread items");
     HIP_TRY(upload(&D.reduces, S.reduces.data(), S.reduces.size(), s, bytes), "upload spread reduces");
     HIP_TRY(upload(&D.interp_items, S.interp_items.data(), S.interp_items.size(), s, bytes), "upload interp groups");
@@ -300,7 +301,7 @@ ddi_status ddi_plan(const ddi_params* params, void* stream, ddi_plan_t* out) {
   ddi::RingTables rings;
   try {
     const bool by_rings = params->dim == 3 && params->prec == DDI_FP64;
-    msg = ddi::build_tables(*params, P.H, &st, !by_rings);
+    msg = ddi::build_tables(*params, P.H, &st, !by_rings, false);
     if (st == DDI_OK && by_rings) {
       msg = ddi::build_rings(P.H, static_cast<int>(params->n_pol), rings);
       if (!msg.empty()) st = DDI_ENOTSUP;

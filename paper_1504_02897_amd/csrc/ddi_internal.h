@@ -154,8 +154,8 @@ struct Schedule {
   std::vector<SpreadItem> items;
   std::vector<ReduceItem> reduces;
   int32_t nslots = 0;
-  // tile-owned interpolation: one partial sum per list entry; the list positions of node q
-  // are gpos[gptr[q] .. gptr[q+1]) (increasing)
+  // the list positions of node q are gpos[gptr[q] .. gptr[q+1]) (increasing); on request only: no
+  // kernel gathers by tile entries
   std::vector<int32_t> gptr;
   std::vector<int32_t> gpos;
   // row-window form (see HostTables::row_windows): per list entry i, ent[2i] = node and
@@ -230,9 +230,16 @@ inline bool interp_by_rings(const HostTables& H, bool fp64) { return H.dim == 3 
 inline bool uses_weight_rows(const HostTables& H) { return H.row_windows && kSpreadMfma; }
 
 // Builds every host table of a plan.  Returns an empty string on success or an error message.
-// interp_lists = false leaves out the node-owned interpolation's groups and the per-node entry lists,
-// which the interpolation by rings does not use.
-std::string build_tables(const ddi_params& p, HostTables& t, int* status, bool interp_lists = true);
+// interp_lists = false leaves out the node-owned interpolation's groups, which the interpolation by rings
+// does not use; entry_lists = false the positions of every node's entries in the spread's list, which no
+// plan uploads.
+std::string build_tables(const ddi_params& p, HostTables& t, int* status, bool interp_lists = true,
+                         bool entry_lists = true);
+
+// Per node, the positions of its entries (in entry order): those of node q are pos[ptr[q] .. ptr[q+1]);
+// entry i belongs to node[i * stride].
+void entry_positions(const int32_t* node, int stride, size_t count, int64_t M, std::vector<int32_t>& ptr,
+                     std::vector<int32_t>& pos);
 
 // Builds the ring schedules of a 3D plan from its tables (npol = polar nodes of the rule).
 std::string build_rings(const HostTables& t, int npol, RingTables& out);

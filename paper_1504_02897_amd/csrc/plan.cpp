@@ -222,7 +222,7 @@ void build_windows(const HostTables& t, Used used, Schedule& S) {
 // `chunk` nodes are split into chunks whose partial tiles are summed by reduce items.
 template <typename Used>
 std::string build_spread_schedule(const HostTables& t, const std::vector<int64_t>& tile_order, Used used,
-                                  bool interp_lists, Schedule& S) {
+                                  bool entry_lists, Schedule& S) {
   const int64_t M = t.M;
   const int64_t ntile_total = static_cast<int64_t>(t.ntiles[0]) * t.ntiles[1] * t.ntiles[2];
   // tiles that a support meets on an axis, each once (on an axis of one tile it may come round to its first)
@@ -333,20 +333,21 @@ std::string build_spread_schedule(const HostTables& t, const std::vector<int64_t
       }
     }
   }
-  if (!interp_lists) return "";
-  // per node, the positions of its entries in the list (in list order)
-  S.gptr.assign(M + 1, 0);
-  for (int32_t q : S.list) S.gptr[q + 1]++;
-  for (int64_t q = 0; q < M; ++q) S.gptr[q + 1] += S.gptr[q];
-  S.gpos.assign(S.list.size(), 0);
-  {
-    std::vector<int32_t> fillg(S.gptr.begin(), S.gptr.end() - 1);
-    for (size_t i = 0; i < S.list.size(); ++i) S.gpos[fillg[S.list[i]]++] = static_cast<int32_t>(i);
-  }
+  if (entry_lists) entry_positions(S.list.data(), 1, S.list.size(), M, S.gptr, S.gpos);
   return "";
 }
 
 }  // namespace
+
+void entry_positions(const int32_t* node, int stride, size_t count, int64_t M, std::vector<int32_t>& ptr,
+                     std::vector<int32_t>& pos) {
+  ptr.assign(M + 1, 0);
+  for (size_t i = 0; i < count; ++i) ptr[node[i * stride] + 1]++;
+  for (int64_t q = 0; q < M; ++q) ptr[q + 1] += ptr[q];
+  pos.assign(count, 0);
+  std::vector<int32_t> fill(ptr.begin(), ptr.end() - 1);
+  for (size_t i = 0; i < count; ++i) pos[fill[node[i * stride]]++] = static_cast<int32_t>(i);
+}
 
 std::vector<double> twiddle_table(int n) {
   std::vector<double> t(2 * n);
@@ -358,7 +359,7 @@ std::vector<double> twiddle_table(int n) {
   return t;
 }
 
-std::string build_tables(const ddi_params& p, HostTables& t, int* status, bool interp_lists) {
+std::string build_tables(const ddi_params& p, HostTables& t, int* status, bool interp_lists, bool entry_lists) {
   *status = DDI_EINVAL;
   if (p.dim != 2 && p.dim != 3) return "dim must be 2 or 3";
   const int d = p.dim;
@@ -648,7 +649,7 @@ std::string build_tables(const ddi_params& p, HostTables& t, int* status, bool i
     build_windows(t, used, S);
     std::string err;
     if (interp_lists) err = build_interp_schedule(t, key, used, S);
-    if (err.empty()) err = build_spread_schedule(t, tile_order, used, interp_lists, S);
+    if (err.empty()) err = build_spread_schedule(t, tile_order, used, entry_lists, S);
     if (!err.empty()) return err;
   }
   *status = DDI_OK;

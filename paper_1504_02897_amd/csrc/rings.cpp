@@ -181,13 +181,7 @@ std::string build_one(const HostTables& t, const std::vector<int32_t>& order, co
   }
   R.interp_cut = order_items(R.interp, nt1);
   // per node, the positions of its entries (in column order)
-  const int32_t ne = static_cast<int32_t>(R.ent.size() / 2);
-  R.gptr.assign(t.M + 1, 0);
-  for (int32_t p = 0; p < ne; ++p) R.gptr[R.ent[2 * p] + 1]++;
-  for (int64_t q = 0; q < t.M; ++q) R.gptr[q + 1] += R.gptr[q];
-  R.gpos.assign(R.gptr[t.M], 0);
-  std::vector<int32_t> fill(R.gptr.begin(), R.gptr.end() - 1);
-  for (int32_t p = 0; p < ne; ++p) R.gpos[fill[R.ent[2 * p]]++] = p;
+  entry_positions(R.ent.data(), 2, R.ent.size() / 2, t.M, R.gptr, R.gpos);
   return "";
 }
 
