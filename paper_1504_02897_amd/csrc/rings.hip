@@ -73,7 +73,7 @@ __global__ void __launch_bounds__(256, 6) k_ring_interp(const Cd* __restrict__ F
                                                       const double* __restrict__ wz, const int4* __restrict__ refs,
                                                       const RingItem* __restrict__ items,
                                                       const int32_t* __restrict__ cut, const int2* __restrict__ ent,
-                                                      int nf1, int nf2, int nt1, int z0, int nz,
+                                                      int nf1, int nf2, int nt1, int z0,
                                                       Cd* __restrict__ part) {
   constexpr int AS = kRingSpan + 1;
   __shared__ double wa[16 * AS];
@@ -95,29 +95,28 @@ __global__ void __launch_bounds__(256, 6) k_ring_interp(const Cd* __restrict__ F
     y = static_cast<unsigned>(dy) < kWMax ? row[kWMax + dy] : 0.0;
   };
   int2 rec = load_ent(0), rec1 = load_ent(32);
-  // the block's grid values at the wave's 16 positions; positions past the window carry zero
-  // weights and are not read (the transforms never wrote them)
+  // the block's grid values at the wave's 16 positions; a block never reaches past the window (both end
+  // on multiples of four positions), so all of them were written by the transforms
   Cd f[kRingKs];
   {
     const Cd* row = F + (static_cast<int64_t>(it.col / nt1 * 8 + 2 * v + (lr >> 3)) * nf1 + (it.col % nt1 * 8 + (lr & 7))) * nf2;
     int zb = z0 + it.zs;
     if (zb >= nf2) zb -= nf2;
-    if (zb + 4 * it.ks <= nf2 && it.zs + 4 * it.ks <= nz) {
+    if (zb + 4 * it.ks <= nf2) {
       row += zb + lk;
 #pragma unroll
       for (int s = 0; s < kRingKs; ++s) {
         if (s >= it.ks) break;
         f[s] = row[4 * s];
       }
-    } else {
+    } else {                                 // round the end of the axis (at most twice: 32 positions, nf2 >= 16)
 #pragma unroll
       for (int s = 0; s < kRingKs; ++s) {
-        const int zr = it.zs + 4 * s + lk;
-        const bool in = s < it.ks && (zr < nz || nz == nf2);
-        int z = z0 + zr;
+        if (s >= it.ks) break;
+        int z = zb + 4 * s + lk;
         if (z >= nf2) z -= nf2;
         if (z >= nf2) z -= nf2;
-        f[s] = in ? row[z] : Cd{0, 0};
+        f[s] = row[z];
       }
     }
   }
@@ -212,7 +211,7 @@ hipError_t ring_interp(DevicePlan& P, int which, Cd* out, const double* scale, d
     hipLaunchKernelGGL(k_ring_interp, dim3(D.ninterp), dim3(256), 0, s, reinterpret_cast<const Cd*>(P.fine), rows,
                        stride, P.ring_wz, reinterpret_cast<const int4*>(D.refs), D.interp, D.interp_cut,
                        reinterpret_cast<const int2*>(D.ent), H.nf[1], H.nf[2], H.ntiles[1], H.sched[which].z0,
-                       H.sched[which].nz, part);
+                       part);
     DDI_CHECK(hipGetLastError());
   }
   const int blocks = static_cast<int>((H.M + 255) / 256);
