@@ -244,6 +244,27 @@ void entry_positions(const int32_t* node, int stride, size_t count, int64_t M, s
 // Builds the ring schedules of a 3D plan from its tables (npol = polar nodes of the rule).
 std::string build_rings(const HostTables& t, int npol, RingTables& out);
 
+// Morton (Z-order) key of a block coordinate, each below 2^20.
+uint64_t morton3(uint32_t x, uint32_t y, uint32_t z);
+
+// Cuts a list in spatial order into kXcds contiguous regions of about equal work: region x takes the items
+// [cut[x], cut[x + 1]).  Workgroups go to the XCDs in turn, so each XCD, with its own L2, works through one
+// compact region of the grid and its L2 sees the reuse.
+constexpr int kXcds = 8;
+template <typename Item, typename Work>
+std::vector<int32_t> xcd_cuts(const std::vector<Item>& items, Work work) {
+  int64_t total = 0, acc = 0;
+  for (const Item& it : items) total += work(it);
+  std::vector<int32_t> cut(kXcds + 1, static_cast<int32_t>(items.size()));
+  cut[0] = 0;
+  int seg = 1;
+  for (size_t i = 0; i < items.size() && seg < kXcds; ++i) {
+    acc += work(items[i]);
+    while (seg < kXcds && acc * kXcds >= total * seg) cut[seg++] = static_cast<int32_t>(i + 1);
+  }
+  return cut;
+}
+
 // Accurate e^{-2 pi i k / n}, k in [0, n), interleaved (re, im).
 std::vector<double> twiddle_table(int n);
 

@@ -13,6 +13,7 @@
 
 #include "fft.h"
 #include "fft_regs.h"
+#include "wave.h"
 
 namespace ddi {
 
@@ -90,17 +91,11 @@ template <typename T, int N>
 using LdsElem = typename std::conditional<SplitExchange<T, N>::value, T, C<T>>::type;
 
 // Barrier between the LDS writes and reads of an exchange: the whole workgroup, or (WAVE) only
-// the wave, when every line lies inside one wave (LDS operations of a wave complete in order;
-// the fences keep the compiler from moving them across the barrier).
+// the wave, when every line lies inside one wave.
 template <bool WAVE>
 __device__ __forceinline__ void lds_sync() {
-  if constexpr (WAVE) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else {
-    __syncthreads();
-  }
+  if constexpr (WAVE) lds_sync_wave();
+  else __syncthreads();
 }
 
 // One LDS exchange between radix passes: the thread's R1 values (grouped for radix Rs,

@@ -20,6 +20,7 @@
 #include <cstdint>
 
 #include "fft.h"
+#include "wave.h"
 
 namespace ddi {
 
@@ -433,14 +434,6 @@ __device__ inline double row_load(__amdgpu_buffer_rsrc_t rows, unsigned off) {
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rows, off, 0, 0));
   else
     return static_cast<double>(__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rows, off, 0, 0)));
-}
-
-// LDS barrier of a one-wave workgroup: LDS operations of a wave complete in order; the fences
-// keep the compiler from moving them across.
-__device__ __forceinline__ void lds_sync_wave() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Matrix-core form of the spread (FP64, 3D, weight rows): for a tile

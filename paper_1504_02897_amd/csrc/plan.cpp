@@ -76,37 +76,26 @@ double es_fourier(double m, int nf, int w, double beta, const std::vector<double
   return static_cast<double>(2.0L * 0.5L * half * acc);
 }
 
-// Dispatch order for work items that are listed in spatial order: cut the list into
-// kXcd contiguous segments of about equal work and interleave them, so that with the
-// round-robin assignment of workgroups to XCDs (workgroup b runs on XCD b mod kXcd)
-// each XCD works through one compact region of the grid and its L2 sees the reuse.
-// Shorter segments are padded with `pad` items, which the kernels skip.
+// Dispatch order for work items that are listed in spatial order: their regions (xcd_cuts) interleaved, since
+// workgroup b runs on XCD b mod kXcds.  Shorter regions are padded with `pad` items, which the kernels skip.
 template <typename Item, typename Work>
 std::vector<Item> xcd_order(const std::vector<Item>& items_in, Work work, const Item& pad, bool heavy_first = false) {
-  constexpr int kXcd = 8;
-  if (items_in.size() < 2 * kXcd) return items_in;
+  if (items_in.size() < 2 * kXcds) return items_in;
   std::vector<Item> items = items_in;
-  double total = 0.0;
-  for (const Item& it : items) total += work(it);
-  std::vector<size_t> cut(kXcd + 1, items.size());
-  cut[0] = 0;
-  double acc = 0.0;
-  int seg = 1;
-  for (size_t i = 0; i < items.size() && seg < kXcd; ++i) {
-    acc += work(items[i]);
-    if (acc >= total * seg / kXcd) cut[seg++] = i + 1;
-  }
+  const std::vector<int32_t> cut = xcd_cuts(items, work);
   if (heavy_first)   // inside each region, the heaviest items first (the long ones start early)
-    for (int x = 0; x < kXcd; ++x)
+    for (int x = 0; x < kXcds; ++x)
       std::stable_sort(items.begin() + cut[x], items.begin() + cut[x + 1],
                        [&](const Item& a, const Item& b) { return work(a) > work(b); });
-  size_t longest = 0;
-  for (int x = 0; x < kXcd; ++x) longest = std::max(longest, cut[x + 1] - cut[x]);
-  std::vector<Item> out(longest * kXcd, pad);
-  for (int x = 0; x < kXcd; ++x)
-    for (size_t j = 0; j < cut[x + 1] - cut[x]; ++j) out[j * kXcd + x] = items[cut[x] + j];
+  int longest = 0;
+  for (int x = 0; x < kXcds; ++x) longest = std::max(longest, cut[x + 1] - cut[x]);
+  std::vector<Item> out(static_cast<size_t>(longest) * kXcds, pad);
+  for (int x = 0; x < kXcds; ++x)
+    for (int j = 0; j < cut[x + 1] - cut[x]; ++j) out[static_cast<size_t>(j) * kXcds + x] = items[cut[x] + j];
   return out;
 }
+
+}  // namespace
 
 // Morton (Z-order) key of a 3D block coordinate (each coordinate < 2^20): consecutive
 // keys stay compact in all three directions, so work that runs at the same time on one
@@ -123,8 +112,6 @@ uint64_t morton3(uint32_t x, uint32_t y, uint32_t z) {
   };
   return (spread(x) << 2) | (spread(y) << 1) | spread(z);
 }
-
-}  // namespace
 
 namespace {
 
@@ -298,7 +285,7 @@ std::string build_spread_schedule(const HostTables& t, const std::vector<int64_t
   // items are long (about 32 entries or more on average), else the Morton order is kept
   {
     const bool heavy_first = count[ntile_total] >= 32 * static_cast<int64_t>(S.items.size());
-    S.items = xcd_order(S.items, [](const SpreadItem& it) { return 16.0 + it.count; }, SpreadItem{-1, 0, 0, -1},
+    S.items = xcd_order(S.items, [](const SpreadItem& it) { return int64_t(16) + it.count; }, SpreadItem{-1, 0, 0, -1},
                         heavy_first);
   }
 #else

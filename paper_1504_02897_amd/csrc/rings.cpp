@@ -14,24 +14,12 @@ namespace ddi {
 
 namespace {
 
-constexpr int kXcds = 8;
-
-uint64_t morton3(uint32_t x, uint32_t y, uint32_t z) {
-  auto spread = [](uint64_t v) {             // ten bits per coordinate, three positions apart
-    uint64_t o = 0;
-    for (int b = 0; b < 10; ++b) o |= (v >> b & 1) << (3 * b);
-    return o;
-  };
-  return spread(x) << 2 | spread(y) << 1 | spread(z);
-}
-
 // Work of an item in units of one node entry: a ring reference costs the matrix products of its
 // column, about four entries' worth.
 int64_t work_of(const RingItem& it) { return it.nent + 4 * static_cast<int64_t>(it.nref) + 16; }
 
-// Puts the items in Morton order of (column, block) and cuts the list into eight regions of about
-// equal work, one per XCD (workgroup b runs on XCD b mod 8): an XCD works in one compact region,
-// front to back, and its L2 keeps the weight rows and grid rows that neighbouring items share.
+// Puts the items in Morton order of (column, block) and cuts the list into one region per XCD: an XCD works in
+// one compact region, front to back, and its L2 keeps the weight rows and grid rows that neighbouring items share.
 std::vector<int32_t> order_items(std::vector<RingItem>& items, int nt1) {
   std::vector<std::pair<uint64_t, int32_t>> key(items.size());
   for (size_t i = 0; i < items.size(); ++i) {
@@ -46,14 +34,7 @@ std::vector<int32_t> order_items(std::vector<RingItem>& items, int nt1) {
     total += work_of(out[i]);
   }
   items.swap(out);
-  std::vector<int32_t> cut(kXcds + 1, static_cast<int32_t>(items.size()));
-  cut[0] = 0;
-  int64_t acc = 0;
-  int seg = 1;
-  for (size_t i = 0; i < items.size() && seg < kXcds; ++i) {
-    acc += work_of(items[i]);
-    while (seg < kXcds && acc * kXcds >= total * seg) cut[seg++] = static_cast<int32_t>(i + 1);
-  }
+  std::vector<int32_t> cut = xcd_cuts(items, work_of);
   // the items far above the mean (the columns around k = 0 hold whole rings) go first in a region
   const int64_t heavy = 2 * total / std::max<int64_t>(1, static_cast<int64_t>(items.size()));
   for (int x = 0; x < kXcds; ++x) {

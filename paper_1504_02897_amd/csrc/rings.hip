@@ -14,19 +14,12 @@
 #include <cstdint>
 
 #include "ddi_internal.h"
+#include "wave.h"
 
 namespace ddi {
 
 using Cd = Complex<double>;
 typedef double dbl4r __attribute__((ext_vector_type(4)));
-
-// LDS barrier within a wave: LDS operations of a wave complete in order; the fences keep the
-// compiler from moving them across.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // x + its value in the lane whose number differs by the DPP pattern (within eight lanes)
 template <int CTRL>
@@ -150,7 +143,7 @@ __global__ void __launch_bounds__(256, 6) k_ring_interp(const Cd* __restrict__ F
     rec = rec1;
     if (e0 + 32 < it.nent) load_w(rec, wx, wy);          // the next round's weights
     if (e0 + 64 < it.nent) rec1 = load_ent(e0 + 64);
-    wave_sync();
+    lds_sync_wave();
     const double* wyr = wyl[v] + e8 * 8;
     double sr = 0.0, si = 0.0;
 #pragma unroll
@@ -163,7 +156,7 @@ __global__ void __launch_bounds__(256, 6) k_ring_interp(const Cd* __restrict__ F
     si = sum8(si * wxc);
     const int e = e0 + 8 * v + e8;
     if (u < 2 && e < it.nent) reinterpret_cast<double*>(part + (static_cast<int64_t>(it.ent0) + e))[u] = u == 0 ? sr : si;
-    wave_sync();
+    lds_sync_wave();
   }
 }
 
