@@ -29,16 +29,56 @@ FP32_PEAK_TFLOPS = 157.3
 METRIC = "DDI evals/s at 128³ (FP64 vs mixed, rel L∞ ≤1e-6); fwd+adjoint ms"
 
 
-def stage_model(plan, real_bytes, cplx_bytes):
+def kept_nodes(index, quad):
+    """The nodes that the operator visits: of each +-k pair the first in the rule's order, and the nodes
+    without a partner (3D)."""
+    import numpy as np
+    _, npol, nazi = quad
+    if nazi % 2:
+        return np.ones(len(index), dtype=bool)
+    a, b, c = np.asarray(index, dtype=np.int64).T
+    mine = (a * npol + b) * nazi + c
+    other = (a * npol + npol - 1 - b) * nazi + (c + nazi // 2) % nazi
+    return (mine < other) | ~np.isin(other, mine)
+
+
+def ring_counts(plan, quad):
+    """Of the operator's nodes on a 3D plan: the pairs of an 8 x 8 column of the fine grid and a ring (the
+    nodes of one radial and polar index) over it, and the entries (column, node)."""
+    import numpy as np
+    index, k, _ = plan.nodes()
+    kept = kept_nodes(index, quad)
+    index, k = np.asarray(index, dtype=np.int64)[kept], np.asarray(k)[kept]
+    w, nf = plan.info["width"], plan.info["n_fine"]
+    first, last = [], []
+    for a in range(2):
+        tau = k[:, a] * (2.0 * plan.L[a] / plan.shape[a]) * nf[a] / (2.0 * math.pi)
+        l0 = np.ceil(tau - 0.5 * w).astype(np.int64) % nf[a]
+        first.append(l0 // 8)
+        last.append((l0 + w - 1) // 8)
+    ring = index[:, 0] * quad[1] + index[:, 1]
+    nt = [nf[0] // 8, nf[1] // 8]
+    keys = []
+    for i in range(3):                # a support meets at most three columns per axis
+        for j in range(3):
+            on = (first[0] + i <= last[0]) & (first[1] + j <= last[1])
+            col = (first[0] + i) % nt[0] * nt[1] + (first[1] + j) % nt[1]
+            keys.append((ring * (nt[0] * nt[1]) + col)[on])
+    keys = np.concatenate(keys)
+    return int(np.unique(keys).size), int(keys.size)
+
+
+def stage_model(plan, real_bytes, cplx_bytes, quad):
     """Algorithmic HBM bytes and flops of each stage of one apply.
 
     FFT passes: the active part of each line is read and written once, over the lines at
     the last-axis positions the operator needs (the window of the kept half of the nodes).
-    Interpolation: the fine grid's window is read once, plus node records and node values.
-    Spread: the window is written once, plus node records, node values and the tile lists.  Flops of
-    interpolation/spread: 4 per (node, grid point) pair (a real weight times a complex
-    value accumulated), w^d pairs per node, over the nodes the operator visits (one per
-    +-k pair); of an FFT pass: 5 n log2 n per line.
+    Interpolation: the fine grid's window is read once, plus node records and node values; by rings (FP64
+    in 3D) two weight rows per node, the (column, ring) references and the (column, node) entries with
+    their places in the gather.  Spread: the window is written once, plus weight rows and entries (3D) or
+    node records and tile lists (2D), and node values.  Flops, 4 per product of a real weight and a complex
+    value: w^d products per node the operator visits (one per +-k pair); by rings w per column position
+    and (column, ring) pair, then w^2 per node.  Of an FFT pass: 5 n log2 n per line.
     """
     N = [1] * (3 - plan.dim) + list(plan.shape)
     nf = list(plan.info["n_fine"])
@@ -57,8 +97,14 @@ def stage_model(plan, real_bytes, cplx_bytes):
     st["fft_axis1_t2"] = (N[0] * N[1] * z * c + N[0] * nf[1] * z * c, fftf(nf[1], N[0] * z))
     st["fft_axis0_t2"] = ((N[0] * nf[1] * z * c + nf[0] * nf[1] * z * c) if nf[0] > 1 else 0,
                           fftf(nf[0], nf[1] * z))
-    st["interp"] = (nf[0] * nf[1] * z * c + M * (rec + c + 8), 4.0 * M * w ** d)
-    st["spread"] = (nf[0] * nf[1] * z * c + M * (rec + c) + 4 * plan.info["spread_entries"], 4.0 * M * w ** d)
+    if d == 3 and real_bytes == 8:
+        pairs, entries = ring_counts(plan, quad)
+        st["interp"] = (nf[0] * nf[1] * z * c + M * (2 * 16 * 8 + 8 + c) + 16 * pairs + 12 * entries,
+                        4.0 * 64 * w * pairs + 4.0 * w * w * M)
+    else:
+        st["interp"] = (nf[0] * nf[1] * z * c + M * (rec + c + 8), 4.0 * M * w ** d)
+    rows, entry = (3 * 16 * real_bytes, 8) if d == 3 else (rec, 4)
+    st["spread"] = (nf[0] * nf[1] * z * c + M * (rows + c) + entry * plan.info["spread_entries"], 4.0 * M * w ** d)
     st["spread_reduce"] = (0.0, 0.0)
     st["fft_axis0_t1"] = st["fft_axis0_t2"]
     st["fft_axis1_t1"] = st["fft_axis1_t2"]
@@ -409,7 +455,7 @@ def other_workloads(args, torch, np, I, DDIPlan):
     ms = time_steps(lambda: p.apply(r, out=o), reps, 3, torch)
     fa = time_steps(lambda: (p.apply(r, out=o), p.apply_adjoint(o, out=a)), max(3, reps // 2), 2, torch)
     st = p.profile(r, reps=3)
-    model = stage_model(p, 4, 8)
+    model = stage_model(p, 4, 8, wl["quad"])
     dom = max(st, key=st.get)
     p.apply(r, out=o)
     g4 = golden(name, args.seed)
@@ -665,12 +711,12 @@ def main():
                 else err_at_points(phim, g2["points"], g2["phi_f32in"], g2["phi_absmax"]))
     print(f"[bench] mixed {ms32:.3f} ms/eval, rel Linf vs fp64 {err_mixed:.2e}", file=sys.stderr, flush=True)
 
-    model64 = stage_model(p64, 8, 16)
+    model64 = stage_model(p64, 8, 16, wl["quad"])
     dom = max(stages64, key=stages64.get)
     roof = roofline_of(dom, stages64[dom], model64, FP64_PEAK_TFLOPS)
     roof["traffic"] = measured_traffic("c2_128", "fp64", dom)
     roof["stages_ms"] = {k: round(v, 4) for k, v in stages64.items()}
-    model32 = stage_model(p32, 4, 8)
+    model32 = stage_model(p32, 4, 8, wl["quad"])
     dom32 = max(stages32, key=stages32.get)
     roof32 = roofline_of(dom32, stages32[dom32], model32, FP32_PEAK_TFLOPS)
     roof32["traffic"] = measured_traffic("c2_128", "mixed", dom32)

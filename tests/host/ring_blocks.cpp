@@ -1,8 +1,8 @@
 // Host-only driver of the ring schedules' blocks, for the CPU tests: builds a 3D plan's tables and rings
-// and prints, per schedule, "which blocks longest full outside faults entries": the number of interpolation blocks,
+// and prints, per schedule, "which blocks longest full outside faults entries pairs": the number of interpolation blocks,
 // the entries of the longest, how many rings have more entries over one column than a block takes, how
 // many blocks reach beyond the last-axis window, and how many entries are not a (column, node) pair of
-// the tile lists met once, at the right offsets, and the number of entries.
+// the tile lists met once, at the right offsets, the number of entries and of (column, ring) pairs.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -67,7 +67,7 @@ int main(int argc, char** argv) {
     }
     faults += mine != tiles;
     for (const auto& o : over) full += o.second > kRingInterpEntries;
-    std::printf("%d %zu %d %d %d %d %zu\n", which, S.interp.size(), longest, full, outside, faults, mine.size());
+    std::printf("%d %zu %d %d %d %d %zu %zu\n", which, S.interp.size(), longest, full, outside, faults, mine.size(), over.size());
   }
   return 0;
 }

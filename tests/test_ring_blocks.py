@@ -47,7 +47,7 @@ def test_no_block_is_longer_than_its_limit(blocks, n, quad, tol, split, mask, fu
     assert r.returncode == 0, r.stdout + r.stderr
     lines = [[int(v) for v in ln.split()] for ln in r.stdout.splitlines()]
     assert len(lines) == 2
-    for _, count, longest, over, outside, faults, entries in lines:
+    for _, count, longest, over, outside, faults, entries, _ in lines:
         assert count > 0 and outside == 0 and faults == 0
         assert longest <= min(max(entries // 4096, BLOCK_ENTRIES), 1024)
         assert (over > 0) == full
