@@ -223,9 +223,14 @@ struct HostTables {
   double mv[3] = {0, 0, 1};
 };
 
-// Kernel selection shared by the plan upload and the drivers.  FP64 in 3D interpolates by rings, FP32 in
-// 3D node by node: its narrower kernel leaves few nodes of a ring over a column (256^3, w = 8: 291 + 11
-// us by rings against 248; 128^3: 51 + 6 against 60).
+// Kernel selection shared by the plan upload and the drivers.  FP64 in 3D interpolates by rings at every
+// kernel width.  Against whole 8 x 8 x 8 tiles contracted per (tile, node) entry (us, tiles / rings), type-2:
+// 64^3 44.5 / 44.7, 48.5 / 46.4, 66 / 51 at w = 4, 8, 14; 128^3 237 / 222, 265 / 246, 399 / 297.  Apply: 64^3
+// 88 / 87, 100 / 96, 115 / 105; 128^3 314 / 311, 301 / 304, 323 / 329, 335 / 332, 440 / 394 at w = 4, 6, 8, 9, 14: the
+// tiles left all of the spread's tables in the Infinity Cache, the rings only two of three weight rows, so
+// at 128^3 the spread gives back what a narrow kernel's interpolation gains (16 x 16 x 1024 rule, w = 4: 248 / 260).
+// FP32 in 3D interpolates node by node: there rings gained 3 us at 128^3 (w = 8: 60 / 57) and lost 54 at 256^3
+// (248 / 302).
 inline bool interp_by_rings(const HostTables& H, bool fp64) { return H.dim == 3 && fp64; }
 inline bool uses_weight_rows(const HostTables& H) { return H.row_windows && kSpreadMfma; }
 
@@ -350,7 +355,7 @@ struct DevicePlan {
   void* fine = nullptr;          // Complex<T>[nf0*nf1*nf2]
   void* gnodes = nullptr;        // Complex<T>[M]
   void* partial = nullptr;       // Complex<T>[nslots][tile volume]
-  void* ipartial = nullptr;      // Complex<double>[spread entries]: interpolation partial sums
+  void* ipartial = nullptr;      // Complex<double>[ring entries]: interpolation partial sums
   void* pads = nullptr;          // T[M + 1][3][kRowLen]: weight rows (one 128-byte line per row in
                                  // FP64), then a zero record that positions outside a window read
   int64_t workspace_bytes = 0;

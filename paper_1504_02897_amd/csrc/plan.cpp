@@ -181,8 +181,8 @@ void build_windows(const HostTables& t, Used used, Schedule& S) {
   }
   // axis-1 window, centred on mode 0 (3D only): the smallest ny with every support inside the
   // signed positions [-ny/2, ny/2) and ny/2 a multiple of the tile extent, so that a tile lies
-  // wholly inside or outside (the matrix-core interpolation multiplies whole tiles, and rows
-  // outside the window are never transformed)
+  // wholly inside or outside (the interpolation by rings multiplies whole 8 x 8 columns, and rows outside
+  // the window are never transformed)
   {
     const int n = t.nf[1];
     S.ny = n;

@@ -51,23 +51,21 @@ constexpr int kGx = 9, kGring = 8 * kGx + 1;
 
 constexpr int kRingKs = kRingSpan / 4;
 
-// One workgroup (four waves) per block of up to 16 rings of a column.  Bound by the latency of its
-// dependent loads (block, references, weight rows) against six workgroups per CU, then by the grid
-// reads (consecutive blocks of a column overlap: 1.4 times the window).  Measured with the gather at
-// 128^3, w = 14, 138404 nodes: 88 + 9 us, against 142 + 20 us for whole 8 x 8 x 8 tiles contracted per
-// (tile, node) entry (2.5 M entries and 2.47 M matrix products; here 0.90 M and 0.58 M); 32^3: 7 + 4
-// against 10 + 6; 96^3: 36 + 6 against 61 + 10.  A fixed set of workgroups stepping through the blocks
-// with the next block's loads in flight needs twice the registers and took 106 us.  Wave v contracts the last axis
-// for the column positions x = 2 v, 2 v + 1 (grid values loaded four lanes per 64-byte run and moved
-// to the lanes of the matrix fragment), then the four waves share the block's entries, eight lanes
-// each (lane u takes the row x = u).
+// One workgroup (four waves) per block of up to 16 references of a column.  Bound by the latency of its
+// dependent loads (block, references, weight rows) against six workgroups per CU, then by the grid reads
+// (consecutive blocks of a column overlap: at 128^3 2.3 times the window for w = 14, 1.4 for w = 8, most of it
+// from L2).  Measured with the gather at 128^3, w = 14, 138404 nodes: 88 + 9 us, against 142 + 20 us for whole
+// 8 x 8 x 8 tiles contracted per (tile, node) entry (2.5 M entries and 2.47 M matrix products; here 0.90 M and
+// 0.68 M); 32^3: 7 + 4 against 10 + 6; 96^3: 36 + 6 against 61 + 10.  A fixed set of workgroups stepping through
+// the blocks with the next block's loads in flight needs twice the registers and took 106 us.  Wave v contracts
+// the last axis for the column positions x = 2 v, 2 v + 1 (grid values loaded four lanes per 64-byte run and
+// moved to the lanes of the matrix fragment), then the four waves share the block's entries, eight lanes each
+// (lane u takes the row x = u).
 __global__ void __launch_bounds__(256, 6) k_ring_interp(const Cd* __restrict__ F, const double* __restrict__ rows,
-                                                      int stride,
-                                                      const double* __restrict__ wz, const int4* __restrict__ refs,
-                                                      const RingItem* __restrict__ items,
+                                                      int stride, const double* __restrict__ wz,
+                                                      const int4* __restrict__ refs, const RingItem* __restrict__ items,
                                                       const int32_t* __restrict__ cut, const int2* __restrict__ ent,
-                                                      int nf1, int nf2, int nt1, int z0,
-                                                      Cd* __restrict__ part) {
+                                                      int nf1, int nf2, int nt1, int z0, Cd* __restrict__ part) {
   constexpr int AS = kRingSpan + 1;
   __shared__ double wa[16 * AS];
   __shared__ Cd G[16 * kGring];
