@@ -60,7 +60,7 @@ void free_plan(ddi::DevicePlan& P) {
       if (p) (void)hipFree(p);
   }
   for (auto& d : P.drings) {
-    void* rp[] = {d.refs, d.ent, d.interp, d.interp_cut, d.gptr, d.gpos};
+    void* rp[] = {d.refs, d.ent, d.interp, d.gptr, d.gpos};
     for (void* p : rp)
       if (p) (void)hipFree(p);
   }
@@ -73,7 +73,7 @@ void free_plan(ddi::DevicePlan& P) {
 template <typename T>
 ddi_status build_device(ddi::DevicePlan& P, hipStream_t s, const ddi::RingTables& rings,
                         std::vector<ddi::NodeRec<T>>& recs, std::vector<std::vector<ddi::Complex<T>>>& tws,
-                        std::vector<T>& rows) {
+                        std::vector<T>& rows, std::vector<ddi::RingItem>* items) {
   const ddi::HostTables& H = P.H;
   int64_t& bytes = P.workspace_bytes;
   std::vector<double> cs(H.M), cs_half(H.M);
@@ -123,14 +123,12 @@ ddi_status build_device(ddi::DevicePlan& P, hipStream_t s, const ddi::RingTables
     auto& Q = P.drings[w];
     HIP_TRY(upload(&Q.refs, R.refs.data(), R.refs.size(), s, bytes), "upload ring references");
     HIP_TRY(upload(&Q.ent, R.ent.data(), R.ent.size(), s, bytes), "upload ring entries");
-    HIP_TRY(upload(&Q.interp, R.interp.data(), R.interp.size(), s, bytes), "upload interpolation items");
-    HIP_TRY(upload(&Q.interp_cut, R.interp_cut.data(), R.interp_cut.size(), s, bytes), "upload interpolation regions");
+    // the regions interleaved: workgroup b, on XCD b mod 8, takes item b / 8 of region b mod 8
+    items[w] = ddi::interleave(R.interp, R.interp_cut, ddi::RingItem{});
+    HIP_TRY(upload(&Q.interp, items[w].data(), items[w].size(), s, bytes), "upload interpolation items");
+    Q.ninterp = static_cast<int>(items[w].size());
     HIP_TRY(upload(&Q.gptr, R.gptr.data(), R.gptr.size(), s, bytes), "upload interp gather");
     HIP_TRY(upload(&Q.gpos, R.gpos.data(), R.gpos.size(), s, bytes), "upload interp gather");
-    // workgroup b takes item b / 8 of the region of XCD b mod 8
-    int longest = 0;
-    for (size_t x = 0; x + 1 < R.interp_cut.size(); ++x) longest = std::max(longest, R.interp_cut[x + 1] - R.interp_cut[x]);
-    Q.ninterp = 8 * longest;
     nentries = std::max(nentries, R.ent.size() / 2);
   }
   if (use_pads) {
@@ -344,9 +342,10 @@ ddi_status ddi_plan(const ddi_params* params, void* stream, ddi_plan_t* out) {
   std::vector<std::vector<ddi::Complex<float>>> tf;
   std::vector<double> pd;
   std::vector<float> pf;
+  std::vector<ddi::RingItem> items[2];
   try {
-    ds = P.mixed ? build_device<float>(P, s, rings, rf, tf, pf)
-                 : build_device<double>(P, s, rings, rd, td, pd);
+    ds = P.mixed ? build_device<float>(P, s, rings, rf, tf, pf, items)
+                 : build_device<double>(P, s, rings, rd, td, pd, items);
   } catch (const std::bad_alloc&) {
     ds = fail(DDI_ENOMEM, "host allocation failed while uploading plan tables");
   }

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -226,7 +227,7 @@ struct HostTables {
 // Kernel selection shared by the plan upload and the drivers.  FP64 in 3D interpolates by rings at every
 // kernel width.  Against whole 8 x 8 x 8 tiles contracted per (tile, node) entry (us, tiles / rings), type-2:
 // 64^3 44.5 / 44.7, 48.5 / 46.4, 66 / 51 at w = 4, 8, 14; 128^3 237 / 222, 265 / 246, 399 / 297.  Apply: 64^3
-// 88 / 87, 100 / 96, 115 / 105; 128^3 314 / 311, 301 / 304, 323 / 329, 335 / 332, 440 / 394 at w = 4, 6, 8, 9, 14: the
+// 88 / 87, 100 / 96, 115 / 105; 128^3 311 / 312, 306 / 308, 325 / 320, 336 / 331, 440 / 394 at w = 4, 6, 8, 9, 14: the
 // tiles left all of the spread's tables in the Infinity Cache, the rings only two of three weight rows, so
 // at 128^3 the spread gives back what a narrow kernel's interpolation gains (16 x 16 x 1024 rule, w = 4: 248 / 260).
 // FP32 in 3D interpolates node by node: there rings gained 3 us at 128^3 (w = 8: 60 / 57) and lost 54 at 256^3
@@ -268,6 +269,18 @@ std::vector<int32_t> xcd_cuts(const std::vector<Item>& items, Work work) {
     while (seg < kXcds && acc * kXcds >= total * seg) cut[seg++] = static_cast<int32_t>(i + 1);
   }
   return cut;
+}
+
+// The items of the regions interleaved, since workgroup b runs on XCD b mod kXcds; shorter regions are padded
+// with `pad` items, which the kernels skip.
+template <typename Item>
+std::vector<Item> interleave(const std::vector<Item>& items, const std::vector<int32_t>& cut, const Item& pad) {
+  int longest = 0;
+  for (int x = 0; x < kXcds; ++x) longest = std::max(longest, cut[x + 1] - cut[x]);
+  std::vector<Item> out(static_cast<size_t>(longest) * kXcds, pad);
+  for (int x = 0; x < kXcds; ++x)
+    for (int j = 0; j < cut[x + 1] - cut[x]; ++j) out[static_cast<size_t>(j) * kXcds + x] = items[cut[x] + j];
+  return out;
 }
 
 // Accurate e^{-2 pi i k / n}, k in [0, n), interleaved (re, im).
@@ -342,10 +355,9 @@ struct DevicePlan {
     RingRef* refs = nullptr;
     int32_t* ent = nullptr;
     RingItem* interp = nullptr;
-    int32_t* interp_cut = nullptr;
     int32_t* gptr = nullptr;
     int32_t* gpos = nullptr;
-    int ninterp = 0;             // workgroups
+    int ninterp = 0;             // workgroups: the regions' items interleaved, with padding
   } drings[2];
   double* ring_wz = nullptr;     // [rings][kWMax]
   void* xyw = nullptr;           // T[M][2][kWMax]: weight rows of axes 0 and 1, without row windows

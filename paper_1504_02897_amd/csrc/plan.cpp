@@ -76,8 +76,7 @@ double es_fourier(double m, int nf, int w, double beta, const std::vector<double
   return static_cast<double>(2.0L * 0.5L * half * acc);
 }
 
-// Dispatch order for work items that are listed in spatial order: their regions (xcd_cuts) interleaved, since
-// workgroup b runs on XCD b mod kXcds.  Shorter regions are padded with `pad` items, which the kernels skip.
+// Dispatch order for work items that are listed in spatial order: their regions (xcd_cuts) interleaved.
 template <typename Item, typename Work>
 std::vector<Item> xcd_order(const std::vector<Item>& items_in, Work work, const Item& pad, bool heavy_first = false) {
   if (items_in.size() < 2 * kXcds) return items_in;
@@ -87,12 +86,7 @@ std::vector<Item> xcd_order(const std::vector<Item>& items_in, Work work, const 
     for (int x = 0; x < kXcds; ++x)
       std::stable_sort(items.begin() + cut[x], items.begin() + cut[x + 1],
                        [&](const Item& a, const Item& b) { return work(a) > work(b); });
-  int longest = 0;
-  for (int x = 0; x < kXcds; ++x) longest = std::max(longest, cut[x + 1] - cut[x]);
-  std::vector<Item> out(static_cast<size_t>(longest) * kXcds, pad);
-  for (int x = 0; x < kXcds; ++x)
-    for (int j = 0; j < cut[x + 1] - cut[x]; ++j) out[static_cast<size_t>(j) * kXcds + x] = items[cut[x] + j];
-  return out;
+  return interleave(items, cut, pad);
 }
 
 }  // namespace

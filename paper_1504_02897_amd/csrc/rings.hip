@@ -64,15 +64,14 @@ constexpr int kRingKs = kRingSpan / 4;
 __global__ void __launch_bounds__(256, 6) k_ring_interp(const Cd* __restrict__ F, const double* __restrict__ rows,
                                                       int stride, const double* __restrict__ wz,
                                                       const int4* __restrict__ refs, const RingItem* __restrict__ items,
-                                                      const int32_t* __restrict__ cut, const int2* __restrict__ ent,
-                                                      int nf1, int nf2, int nt1, int z0, Cd* __restrict__ part) {
+                                                      const int2* __restrict__ ent, int nf1, int nf2, int nt1, int z0,
+                                                      Cd* __restrict__ part) {
   constexpr int AS = kRingSpan + 1;
   __shared__ double wa[16 * AS];
   __shared__ Cd G[16 * kGring];
   __shared__ double wyl[4][64];
-  const int i = cut[blockIdx.x & 7] + static_cast<int>(blockIdx.x >> 3);
-  if (i >= cut[(blockIdx.x & 7) + 1]) return;
-  const RingItem it = items[i];
+  const RingItem it = items[blockIdx.x];
+  if (it.nref == 0) return;                  // padding item
   const int lane = threadIdx.x & 63, v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int k = lane >> 4, j = lane & 15;
   const int e8 = lane >> 3, u = lane & 7;
@@ -200,7 +199,7 @@ hipError_t ring_interp(DevicePlan& P, int which, Cd* out, const double* scale, d
   const int stride = P.pads ? 3 * kRowLen : 2 * kWMax;
   if (D.ninterp > 0) {
     hipLaunchKernelGGL(k_ring_interp, dim3(D.ninterp), dim3(256), 0, s, reinterpret_cast<const Cd*>(P.fine), rows,
-                       stride, P.ring_wz, reinterpret_cast<const int4*>(D.refs), D.interp, D.interp_cut,
+                       stride, P.ring_wz, reinterpret_cast<const int4*>(D.refs), D.interp,
                        reinterpret_cast<const int2*>(D.ent), H.nf[1], H.nf[2], H.ntiles[1], H.sched[which].z0,
                        part);
     DDI_CHECK(hipGetLastError());
